@@ -584,7 +584,7 @@ def measured_traffic(args, name: str, source: str):
     return tr.get("bytes_per_launch") if same else None
 
 
-def kernel_source_sha(source: str = "hmm_kernels.hip") -> str:
+def kernel_source_sha(source: str = "hmm_msv.hip") -> str:
     import hashlib
     p = os.path.join(ROOT, "paper_2111_06340_amd", "csrc", source)
     with open(p, "rb") as f:

@@ -114,10 +114,11 @@ __device__ __forceinline__ void maxplus_steps_i(int b, int (&bs)[6]) {
 
 __device__ __forceinline__ int fl32(int v) { return max(v, kNeg32); }
 
-// The workgroup's next target (thread 0 takes it from the work counter).
-__device__ __forceinline__ int next_target(int32_t *work, int *slot) {
+// The workgroup's next item, the same in all of its waves.
+__device__ __forceinline__ int next_target(const WorkQueue<true> &queue, int *slot) {
+  if (queue.n <= queue.n0) return queue.n;
   __syncthreads();
-  if (threadIdx.x == 0) *slot = atomicAdd(work, 1);
+  if (threadIdx.x == 0) *slot = queue.n0 + atomicAdd(queue.work, 1) * queue.lanes + queue.c;
   __syncthreads();
   return __builtin_amdgcn_readfirstlane(*slot);
 }
@@ -188,9 +189,8 @@ __device__ __forceinline__ void fwd_coop_wave(const DevProfile &P, const DevDb &
   const float mdn = into_next(TR_MDIN, w), ddn = into_next(TR_DDIN, w);
   const float entry_p = P.entry_p;
   const int count = uni(__atomic_load_n(&db.counters[CNT_FWD], __ATOMIC_RELAXED));
-  for (;;) {
-    const int idx = next_target(&db.counters[CNT_WORK_FWD], &sh.slot);
-    if (idx >= count) break;
+  const WorkQueue<true> queue(db, WORK_FWD, count);
+  for (int idx = queue.first(); idx < count; idx = next_target(queue, &sh.slot)) {
     const int t = uni(db.list_fwd[idx]);
     const int L = uni(db.len[t]);
     const LenParams lp = db.lp[L];
@@ -405,9 +405,8 @@ __device__ __forceinline__ void vit32_coop_wave(const DevProfile &P, const DevDb
   }
   const int mdn = into_next(TR_MDIN, w), ddn = into_next(TR_DDIN, w);
   const int count = uni(__atomic_load_n(&db.counters[CNT_OVF], __ATOMIC_RELAXED));
-  for (;;) {
-    const int idx = next_target(&db.counters[CNT_WORK_OVF], &sh.slot);
-    if (idx >= count) break;
+  const WorkQueue<true> queue(db, WORK_OVF, count);
+  for (int idx = queue.first(); idx < count; idx = next_target(queue, &sh.slot)) {
     const int t = uni(db.list_ovf[idx]);
     const int L = uni(db.len[t]);
     const LenParams lp = db.lp[L];

@@ -190,9 +190,8 @@ __global__ void __launch_bounds__(kDecThreads) decode_kernel(DevProfile P, DevDb
   const int cbase = vl * Q;   // first cell of this lane in the Backward layout
 
   const int count = uni(__atomic_load_n(&db.counters[CNT_DEC], __ATOMIC_RELAXED));
-  for (;;) {
-    const int idx = wave_fetch_add(&db.counters[CNT_WORK_DEC], 1);
-    if (idx >= count) break;
+  const WorkQueue<> queue(db, WORK_DEC, count);
+  for (int idx = queue.first(); idx < count; idx = queue.next()) {
     const int t = uni(db.list_vit[idx]);
     const int L = uni(db.len[t]);
     const LenParams lp = db.lp[L];
@@ -723,9 +722,9 @@ __global__ void decode_select(DevDb db, const uint8_t *flags, int mask) {
 __global__ void decode_clear(int32_t *c) {
   if (threadIdx.x == 0) {
     c[CNT_DEC] = 0;
-    c[CNT_WORK_DEC] = 0;
     c[CNT_NDOM] = 0;
   }
+  if (threadIdx.x < kWorkLanes) c[CNT_WORK + (WORK_DEC * kWorkLanes + threadIdx.x) * kWorkStride] = 0;
 }
 
 __global__ void decode_export(const int32_t *c, int32_t *n_dom) {

@@ -38,6 +38,39 @@ __device__ __forceinline__ int wave_fetch_add(int32_t *p, int inc) {
   return uni(atomicAdd(p, lane == 0 ? inc : 0));
 }
 
+__device__ __forceinline__ int num_waves() { return uni((int)gridDim.x * (int)(blockDim.x >> 6)); }
+
+// The items 0 .. n-1 of a stage, handed out to the workers of a launch: its
+// waves, or its blocks (PER_BLOCK).  A worker first takes the item of its own
+// index, counted across the blocks before the waves of a block, so that few
+// items spread over all CUs; the rest come from the stage's work counters, one
+// for the blocks of each XCD (counter c holds the items n0 + lanes k + c: the
+// same mix of lengths everywhere).  With no more items than workers, no counter
+// is used.
+template <bool PER_BLOCK = false>
+struct WorkQueue {
+  int32_t *work;
+  int n, n0, lanes, c;
+  __device__ __forceinline__ WorkQueue(const DevDb &db, int stage, int n_) : n(n_) {
+    n0 = PER_BLOCK ? (int)gridDim.x : num_waves();
+    lanes = min(kWorkLanes, (int)gridDim.x);
+    c = (int)blockIdx.x % lanes;
+    work = db.counters + CNT_WORK + (stage * kWorkLanes + c) * kWorkStride;
+  }
+  __device__ __forceinline__ int first() const {
+    return (PER_BLOCK ? 0 : (uni((int)threadIdx.x) >> 6) * (int)gridDim.x) + (int)blockIdx.x;
+  }
+  // A wave's next item; or in two steps, the bump, whose latency other work may
+  // hide, and the item it brought.  (Asked before a long target instead of
+  // after it, waves with long targets take items that idle ones should have:
+  // 5,000 targets of 77 nodes, all stages, 0.72 against 0.63 ms.)
+  __device__ __forceinline__ int ask() const {
+    return n <= n0 ? 0 : atomicAdd(work, (threadIdx.x & 63) == 0 ? 1 : 0);
+  }
+  __device__ __forceinline__ int item(int asked) const { return n <= n0 ? n : n0 + uni(asked) * lanes + c; }
+  __device__ __forceinline__ int next() const { return item(ask()); }
+};
+
 // --- packed 16-bit arithmetic ------------------------------------------------
 __device__ __forceinline__ uint32_t u16_max(uint32_t a, uint32_t b) {
   return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a),

@@ -80,6 +80,15 @@ int instantiated_q32(int q) {
   return -1;
 }
 
+// MSV instances: every size up to kMaxQDiag in the diagonal layout, these in
+// the striped one.
+int instantiated_msv_striped(int q) {
+  static const int qs[] = {8, 9, 10, 11, 12, 14, 16, 18, 20, 22, 24};
+  for (int v : qs)
+    if (v >= q) return v;
+  return -1;
+}
+
 std::atomic<uint64_t> g_profile_serial{1};
 
 // Device memory the decoding scratch of one database may take.
@@ -193,14 +202,14 @@ inline int w_cell(int Q, int q, int lane) { return lane * Q + q; }
 
 uint32_t pack16(int lo, int hi) { return (uint32_t)(uint16_t)lo | ((uint32_t)(uint16_t)hi << 16); }
 
-// IEEE binary16 encoding of an integer with |v| <= 2048 (exact).
+// IEEE binary16 encoding of v * 2^-11 for an integer with |v| <= 2048 (exact).
 uint16_t half_of_int(int v) {
   if (v == 0) return 0;
   const uint16_t sign = v < 0 ? 0x8000 : 0;
   const unsigned a = (unsigned)(v < 0 ? -v : v);
   const int e = 31 - __builtin_clz(a);                       // a = 2^e * 1.m
   const unsigned m = e <= 10 ? (a << (10 - e)) & 0x3ffu : (a >> (e - 10)) & 0x3ffu;
-  return (uint16_t)(sign | ((unsigned)(e + 15) << 10) | m);
+  return (uint16_t)(sign | ((unsigned)(e - 11 + 15) << 10) | m);
 }
 
 // Host quantisation of a validated descriptor into p's host tables.
@@ -286,12 +295,12 @@ int hmm_profile_upload(const hmm_profile_desc *d, hmm_stream stream, hmm_profile
   // MSV: diagonal layout when M + 1 cells fit a kernel instance of at most
   // kMaxQDiag vectors per lane (it needs one padding cell), else striped.
   const bool msv_diag = q8_of(M + 1) <= kMaxQDiag;
-  const int Qm = msv_diag ? instantiated_q8(q8_of(M + 1)) : instantiated_q8(std::max(q8_of(M), kMaxQDiag));
+  const int Qm = msv_diag ? q8_of(M + 1) : instantiated_msv_striped(q8_of(M));
   if (Q8 < 0 || Q32 < 0 || Qm < 0) {
     delete p;
     return fail(HMM_ERANGE, "M = %d has no kernel instance", M);
   }
-  const size_t n_msv = (size_t)kAlpha * Qm * kWave * (msv_diag ? 2 : 1);  // dwords
+  const size_t n_msv = (size_t)kAlpha * msv_row_dwords(Qm, msv_diag);  // dwords
   const size_t n_vemit = (size_t)kAlpha * 2 * Q8 * kWave;
   const size_t n_vtr = (size_t)TR_N * Q8 * kWave;
   const size_t n_w32emit = (size_t)kAlpha * 2 * Q32 * kWave;
@@ -343,20 +352,27 @@ int hmm_profile_upload(const hmm_profile_desc *d, hmm_stream stream, hmm_profile
   auto isc_cell = [&](int c, int a) -> int { return c + 1 < M ? p->isc16[(size_t)c * kAlpha + a] : kNone; };
   auto lo16 = [](int v) { return v == INT32_MIN ? kNeg16 : v; };
 
-  // MSV scores E = BIAS8 - COST8 as fp16 (exact small integers); padding -1024.
+  // MSV scores E = BIAS8 - COST8 as fp16, exact small integers times 2^-11;
+  // padding cells -1 (-2048), which no cell value outweighs.
   auto msv_e = [&](int c, int a) -> uint16_t {
-    return half_of_int(c < M ? p->bias8 - (int)p->cost8[(size_t)c * kAlpha + a] : -1024);
+    return half_of_int(c < M ? p->bias8 - (int)p->cost8[(size_t)c * kAlpha + a] : -2048);
   };
+  const int msv_row = msv_row_dwords(Qm, msv_diag);
   if (msv_diag) {
     const int P = 2 * Qm * kWave;
+    auto pair = [&](int c, int a) {
+      return (uint32_t)msv_e(c % P, a) | ((uint32_t)msv_e((c + P / 2) % P, a) << 16);
+    };
     for (int a = 0; a < kAlpha; a++)
-      for (int c = 0; c < P; c++)
-        h_msv[(size_t)a * P + c] = (uint32_t)msv_e(c, a) | ((uint32_t)msv_e((c + P / 2) % P, a) << 16);
+      for (int c = 0; c < P; c++) {
+        h_msv[(size_t)a * msv_row + c] = pair(c, a);
+        if (msv_wide(Qm)) h_msv[(size_t)a * msv_row + P + c] = pair(c + 1, a);
+      }
   } else {
     for (int a = 0; a < kAlpha; a++)
       for (int q = 0; q < Qm; q++)
         for (int l = 0; l < kWave; l++)
-          h_msv[(size_t)a * Qm * kWave + pk_index(q, l)] =
+          h_msv[(size_t)a * msv_row + msv_stripe_dword(Qm, q, l)] =
               (uint32_t)msv_e(pk_cell(Qm, q, l, 0), a) | ((uint32_t)msv_e(pk_cell(Qm, q, l, 1), a) << 16);
   }
   for (int a = 0; a < kAlpha; a++)
@@ -959,7 +975,13 @@ int hmm_search(const hmm_profile *p, hmm_db *db, const hmm_thresholds *t, const 
   if (db->tcap > 0) ev = &db->tev[(size_t)(db->trec++ % db->tcap) * 5];
   DevDb chunk[kMaxChunks];
   const int K = db->chunks;
-  for (int k = 0; k < K; k++) chunk[k] = chunk_of(db->dev, db->chunk_at[K][k], db->chunk_at[K][k + 1], k);
+  for (int k = 0; k < K; k++) {
+    chunk[k] = chunk_of(db->dev, db->chunk_at[K][k], db->chunk_at[K][k + 1], k);
+    // the last chunk's stages end the search: their waves take issue priority
+    // by target length (an earlier chunk's share the CUs with the next chunk's
+    // MSV, which they would hold back)
+    chunk[k].prio_by_len = k == K - 1;
+  }
   HIP_TRY(launch_search(p->dev, chunk, K, o, s, db->sync, ev), "kernel launch");
   HIP_TRY(hipEventRecord(db->done, s), "hipEventRecord");
   db->searched = true;
@@ -1010,6 +1032,7 @@ int hmm_search_group(const hmm_profile *const *p, hmm_db *const *db, const hmm_t
     }
     P[i] = p[i]->dev;
     D[i] = chunk_of(d->dev, 0, d->n, 0);
+    D[i].prio_by_len = 1;
     O[i] = DevOut{out[i].msv,    out[i].vit,  out[i].fwd,        out[i].flags,
                   out[i].counts, out[i].bias, t[i].bias_filter, fuse_tail(d->fused_tail, t[i])};
     Y[i] = &d->sync;

@@ -15,7 +15,8 @@ constexpr int kBase8 = 190;         // MSV offset of the N/J start
 constexpr int kNeg16 = -32768;      // int16 "minus infinity"
 constexpr int32_t kNeg32 = -(1 << 30);  // int32 rescore floor
 constexpr int kMaxQ8 = 24;          // 128 cells per packed vector -> M <= 3072
-constexpr int kMaxQDiag = 14;       // largest MSV diagonal-layout instance (LDS 10 KB per vector)
+constexpr int kMaxQDiag = 8;        // largest MSV diagonal-layout instance (LDS 20 KB per vector)
+constexpr int kMaxMsvGroup = 4;     // most profiles of one MSV launch
 constexpr int kMaxQ32 = 48;         // 64 cells per 32-bit vector -> M <= 3072
 
 // Transition planes of the per-cell "into" layout (cell k = node k+1).
@@ -49,9 +50,11 @@ struct DevProfile {
   int32_t dm_max16, dm_max32;
   float entry_p;                // 2/(M(M+1))
   float bias_r[kAlpha];         // composition-bias filter: mean match emission / background
-  // MSV table, packed fp16 scores E = BIAS8 - COST8 (padding cells -1024).
+  // MSV table, packed fp16 scores E = BIAS8 - COST8 times 2^-11 (padding
+  // cells -1), msv_row_dwords per residue.
   // msv_diag = 1: [20][P], P = 128 Qm, dword c = (E_c, E_{(c + P/2) mod P});
-  // msv_diag = 0: [20][Qm][64] in the striped packed layout.
+  // from kMinQWide vectors on [20][2][P], the second row one dword ahead;
+  // msv_diag = 0: the striped packed layout at msv_stripe_dword.
   const uint32_t *msv;
   const uint32_t *vit_emit;     // [20][2][Q8][64] packed i16: msc plane, isc plane
   const uint32_t *vit_tr;       // [TR_N][Q8][64] packed i16
@@ -69,11 +72,20 @@ enum { TR_PRE = TR_N, TR_SUF = TR_N + 1, TR_EXIT = TR_N + 2 };
 
 // Counters in the database scratch (device int32).
 enum {
-  CNT_VIT = 0, CNT_OVF, CNT_FWD, CNT_FWD_PASS, CNT_WORK_VIT, CNT_WORK_OVF, CNT_WORK_FWD,
-  CNT_DEC, CNT_WORK_DEC, CNT_NDOM,   // posterior decoding: list size, work counter, domains found
-  CNT_WORK_MSV,                      // MSV: runs of targets taken
-  CNT_N = 16
+  CNT_VIT = 0, CNT_OVF, CNT_FWD, CNT_FWD_PASS,
+  CNT_DEC, CNT_NDOM,   // posterior decoding: list size, domains found
+  CNT_LISTS = 8,       // the counters above
+  // work counters of the stages, kWorkLanes of them each, kWorkStride apart
+  CNT_WORK = 32
 };
+// Stages that hand their targets out through work counters (WorkQueue).
+enum { WORK_MSV = 0, WORK_BIAS, WORK_VIT, WORK_OVF, WORK_FWD, WORK_DEC, WORK_STAGES };
+// One counter that every wave of the chip bumps is served at about 15 ns a bump
+// (measured: 50,000 targets of 300 nodes taken one by one 0.74 ms, the work
+// itself 0.2 ms), so each stage has one per XCD (blocks go round the 8 XCDs),
+// in a cache line of its own.
+constexpr int kWorkLanes = 8, kWorkStride = 32;
+constexpr int CNT_N = CNT_WORK + WORK_STAGES * kWorkLanes * kWorkStride;
 
 struct DevDb {
   int64_t n;
@@ -91,7 +103,7 @@ struct DevDb {
   const LenParams *lp;          // [max_len + 1]
   const int64_t *coff;          // [n] offset of each target in the caller's residue array
   const int32_t *iperm;         // [n] caller index -> sorted index
-  int32_t prio_by_len;          // 1: the later stages' waves take issue priority by target length
+  int32_t prio_by_len;          // 1: the search stages' waves take issue priority by target length
 };
 
 struct DevOut {
@@ -212,6 +224,24 @@ hipError_t launch_count(const DevProfile &p, const DevDb &db, const hmm_domain *
 // holds one word per thread of the launch (2 x CUs x 1024).
 hipError_t probe_pk16(uint32_t *scratch, int64_t scratch_words, hipStream_t stream, double *ops_per_s,
                       float *ms);
+
+// MSV tables.  Diagonal instances from kMinQWide vectors per lane on keep two
+// copies of each residue's row.
+constexpr int kMinQWide = 6;
+constexpr bool msv_wide(int Q) { return Q >= kMinQWide; }
+constexpr int msv_row_dwords(int Q, bool diag) { return Q * kWave * (diag ? (msv_wide(Q) ? 4 : 2) : 1); }
+// Striped row: dword of vector q of a lane (vectors by fours, then two, then one).
+constexpr int msv_stripe_dword(int Q, int q, int lane) {
+  const int q4 = Q / 4 * 4, q2 = Q / 2 * 2;
+  return q < q4 ? (q & ~3) * kWave + lane * 4 + (q & 3)
+                : q < q2 ? q4 * kWave + lane * 2 + (q - q4) : q2 * kWave + lane;
+}
+constexpr uint32_t kMsvPad2 = 0xbc00bc00u;   // two padding cells
+
+// Enqueue the MSV stage of ng searches of one database by profiles of one
+// instance (ng at most msv_group_max of the profile).
+int msv_group_max(const DevProfile &P);
+hipError_t launch_msv(const DevProfile *P, const DevDb *db, const DevOut *o, int ng, hipStream_t s);
 
 // Number of packed vectors per lane.
 inline int q8_of(int M) { return (M + 2 * kWave - 1) / (2 * kWave); }
