@@ -378,7 +378,7 @@ def main():
             tr = json.load(f)
         # the MSV stage's HBM bytes per search (all of its launches), while
         # the kernel source and the launches per search are the measured ones
-        if (tr.get("workload") == w.name and tr.get("kernel_source_sha") == kernel_source_sha()
+        if (tr.get("workload") == w.name and tr.get("kernel_source_sha") == kernel_source_sha("hmm_msv.hip")
                 and tr.get("header_sha", kernel_source_sha("hmm_device.h")) == kernel_source_sha("hmm_device.h")
                 and tr.get("launches_per_search") == chunks):
             traffic = (tr.get("bytes_per_launch"), tr.get("algorithmic_bytes_per_launch"),
@@ -584,7 +584,7 @@ def measured_traffic(args, name: str, source: str):
     return tr.get("bytes_per_launch") if same else None
 
 
-def kernel_source_sha(source: str = "hmm_msv.hip") -> str:
+def kernel_source_sha(source: str = "hmm_kernels.hip") -> str:
     import hashlib
     p = os.path.join(ROOT, "paper_2111_06340_amd", "csrc", source)
     with open(p, "rb") as f:
