@@ -272,7 +272,8 @@ typedef struct {
  * serialised with the searches on `db`.  On its first call for a database
  * (and when a longer profile needs more) the library allocates a scratch
  * area on the device for the Forward/Backward matrices of the targets in
- * flight -- one slot per resident wave, at most 16 GiB -- which the
+ * flight -- one slot per resident team of 1, 2 or 4 waves (by the profile's
+ * length), at most 16 GiB -- which the
  * database keeps until hmm_db_free.  Errors: HMM_EINVAL (NULL profile, db
  * or out; NULL dom or n_dom; max_dom < 0), HMM_ENOMEM (scratch),
  * HMM_EDEVICE. */
@@ -281,13 +282,13 @@ int hmm_decode(const hmm_profile *p, hmm_db *db, const uint8_t *flags, uint8_t m
 
 /* hmm_decode for callers that cannot allocate device memory: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  The
- * arguments, outputs and results are hmm_decode's; the per-wave scratch is
+ * arguments, outputs and results are hmm_decode's; the per-team scratch is
  * a fixed array of 512 MiB that the library holds on every device it runs
  * on (one copy per device, from the first call on that device until the
  * process ends), so the call allocates nothing.  Slots are sized for the
- * database's longest target; as many waves run as slots fit (a multiple of
- * four): M = 734 with targets up to 1,000 residues gives 80 waves, M = 2,500
- * with targets up to 5,000 residues 4.  Every call on one device shares
+ * database's longest target; as many teams run as slots fit: M = 734 with
+ * targets up to 1,000 residues gives 80 teams of two waves, M = 2,500 with
+ * targets up to 5,000 residues 4 of four.  Every call on one device shares
  * the array and keeps no state in it between calls (nothing in it needs to
  * start at zero), so calls that overlap on one device -- on different
  * streams, or from different threads -- race and give undefined results;

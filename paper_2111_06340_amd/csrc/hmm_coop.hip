@@ -114,15 +114,6 @@ __device__ __forceinline__ void maxplus_steps_i(int b, int (&bs)[6]) {
 
 __device__ __forceinline__ int fl32(int v) { return max(v, kNeg32); }
 
-// The workgroup's next item, the same in all of its waves.
-__device__ __forceinline__ int next_target(const WorkQueue<true> &queue, int *slot) {
-  if (queue.n <= queue.n0) return queue.n;
-  __syncthreads();
-  if (threadIdx.x == 0) *slot = queue.n0 + atomicAdd(queue.work, 1) * queue.lanes + queue.c;
-  __syncthreads();
-  return __builtin_amdgcn_readfirstlane(*slot);
-}
-
 // ============================================================================ Forward
 template <int W>
 struct FwdCoopLds {

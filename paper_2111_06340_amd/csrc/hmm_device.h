@@ -71,6 +71,15 @@ struct WorkQueue {
   __device__ __forceinline__ int next() const { return item(ask()); }
 };
 
+// The workgroup's next item, the same in all of its waves.
+__device__ __forceinline__ int next_target(const WorkQueue<true> &queue, int *slot) {
+  if (queue.n <= queue.n0) return queue.n;
+  __syncthreads();
+  if (threadIdx.x == 0) *slot = queue.n0 + atomicAdd(queue.work, 1) * queue.lanes + queue.c;
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane(*slot);
+}
+
 // --- packed 16-bit arithmetic ------------------------------------------------
 __device__ __forceinline__ uint32_t u16_max(uint32_t a, uint32_t b) {
   return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a),
@@ -172,14 +181,18 @@ __device__ __forceinline__ float affine_scan_fused(float a, const float (&ps)[6]
                : "+v"(a) : "v"(ps[5]));
   return a;
 }
-__device__ __forceinline__ float wave_sum_fused(float v) {
+// The sum across the wave, in lane 63 only.
+__device__ __forceinline__ float wave_sum_lane63(float v) {
   v += dpp_f<kRowShr1, 0xf>(v, 0.0f);
   v += dpp_f<kRowShr2, 0xf>(v, 0.0f);
   v += dpp_f<kRowShr4, 0xf>(v, 0.0f);
   v += dpp_f<kRowShr8, 0xf>(v, 0.0f);
   asm volatile("s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf" : "+v"(v));
   asm volatile("s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf" : "+v"(v));
-  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+  return v;
+}
+__device__ __forceinline__ float wave_sum_fused(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wave_sum_lane63(v)), 63));
 }
 
 // Fused lane shifts: the previous lane's value (0 in lane 0, DPP wave_shr:1

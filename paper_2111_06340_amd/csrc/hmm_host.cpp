@@ -306,7 +306,17 @@ int hmm_profile_upload(const hmm_profile_desc *d, hmm_stream stream, hmm_profile
   const size_t n_w32emit = (size_t)kAlpha * 2 * Q32 * kWave;
   const size_t n_w32tr = (size_t)TR_N * Q32 * kWave;
   const size_t n_ftr = (size_t)(TR_N + 3) * Q32 * kWave;
-  const size_t total = n_msv + n_vemit + n_vtr + n_w32emit + n_w32tr + n_w32emit + n_ftr;
+  // Decoding's own layout (its emissions are f_emit's for teams of one wave)
+  int dqw = 0, dw = 0;
+  if (!decode_split(q32_of(M), &dqw, &dw)) {
+    delete p;
+    return fail(HMM_ERANGE, "M = %d has no decoding instance", M);
+  }
+  const int Qd = dqw * dw;
+  const bool own_demit = dw > 1 || Qd != Q32;
+  const size_t n_demit = own_demit ? (size_t)kAlpha * 2 * Qd * kWave : 0;
+  const size_t n_dtr = (size_t)DT_N * Qd * kWave;
+  const size_t total = n_msv + n_vemit + n_vtr + n_w32emit + n_w32tr + n_w32emit + n_ftr + n_demit + n_dtr + kDecConst;
   std::vector<uint32_t> h(total, 0);
   uint32_t *h_msv = h.data();
   uint32_t *h_vemit = h_msv + n_msv;
@@ -315,6 +325,9 @@ int hmm_profile_upload(const hmm_profile_desc *d, hmm_stream stream, hmm_profile
   int32_t *h_w32tr = h_w32emit + n_w32emit;
   float *h_femit = (float *)(h_w32tr + n_w32tr);
   float *h_ftr = h_femit + n_w32emit;
+  float *h_demit = h_ftr + n_ftr;
+  float *h_dtr = h_demit + n_demit;
+  float *h_dconst = h_dtr + n_dtr;
 
   auto t16 = [&](int node, int which) -> int {  // node 1..M-1
     return p->t16[(size_t)(node - 1) * 7 + which];
@@ -442,6 +455,122 @@ int hmm_profile_upload(const hmm_profile_desc *d, hmm_stream stream, hmm_profile
     }
   }
 
+  // Decoding (DT_*, DC_*): cell (w * 64 + l) * dqw + q in plane w * dqw + q, lane l.
+  {
+    const int n = 64 * Qd, nw = 64 * dqw;   // cells, cells per wave
+    auto dd = [&](int c) { return c < n ? tr_prob(TR_DDIN, c) : 0.0; };   // into delete cell c
+    auto at = [&](int k, int c) -> float & {
+      const int l = c / dqw;
+      return h_dtr[((size_t)k * Qd + (l / 64) * dqw + c % dqw) * kWave + l % 64];
+    };
+    for (int c = 0; c < n; c++) {
+      const int w32 = (c % Q32) * kWave + c / Q32;   // plane entry of the cell in the f_ layouts
+      const bool in32 = c < 64 * Q32;
+      for (int k = 0; k < TR_N; k++) at(k, c) = (float)tr_prob(k, c);
+      at(DT_EXIT, c) = in32 ? h_ftr[(size_t)TR_EXIT * Q32 * kWave + w32] : 0.0f;
+      at(DT_MMO, c) = (float)tr_prob(TR_MMIN, c + 1);
+      at(DT_IMO, c) = (float)tr_prob(TR_IMIN, c + 1);
+      at(DT_DMO, c) = (float)tr_prob(TR_DMIN, c + 1);
+      at(DT_MDO, c) = (float)tr_prob(TR_MDIN, c + 1);
+      at(DT_DDO, c) = (float)tr_prob(TR_DDIN, c + 1);
+      at(DT_PAD, c) = c < M ? 0.0f : -INFINITY;
+      if (own_demit && in32) {
+        const int l = c / dqw;
+        const size_t to = (size_t)((l / 64) * dqw + c % dqw) * kWave + l % 64;
+        for (int a = 0; a < kAlpha; a++)
+          for (int s = 0; s < 2; s++)
+            h_demit[((size_t)a * 2 + s) * Qd * kWave + to] = h_femit[((size_t)a * 2 + s) * Q32 * kWave + w32];
+      }
+    }
+    for (int l = 0; l < 64 * dw; l++) {
+      double acc = 1.0;
+      for (int c = l * dqw; c < (l + 1) * dqw; c++) {
+        acc *= dd(c);
+        at(DT_PRE, c) = (float)acc;
+      }
+      // from the next lane's first delete cell (none past the wave) back to this one
+      acc = l % 64 < 63 ? dd((l + 1) * dqw) : 1.0;
+      bool open = acc > 0.0;
+      for (int c = (l + 1) * dqw - 1; c >= l * dqw; c--) {
+        at(DT_SUF, c) = (float)acc;
+        at(DT_GSUF, c) = open ? 0.0f : -INFINITY;
+        acc *= dd(c);
+        open = open && dd(c) > 0.0;
+      }
+    }
+    std::vector<double> fl(dw), pj(dw), bf(dw), bj(dw);   // per wave: factors through its delete cells and out of them
+    std::vector<char> gf(dw), gj(dw);
+    for (int w = 0; w < dw; w++) {
+      const int a = w * nw, b = a + nw;
+      double acc = 1.0;
+      for (int c = a; c < b; c++) {
+        if (c > a) acc *= dd(c);
+        at(DT_FC, c) = (float)acc;
+      }
+      fl[w] = acc;
+      pj[w] = acc * dd(b);
+      acc = 1.0;
+      bool open = true;
+      for (int c = b - 1; c >= a; c--) {   // acc: from the last delete cell to delete cell c
+        at(DT_GC, c) = open ? 0.0f : -INFINITY;
+        if (c > a) at(DT_BMD, c - 1) = (float)(tr_prob(TR_MDIN, c) * acc);
+        if (c > a) {
+          acc *= dd(c);
+          open = open && dd(c) > 0.0;
+        }
+      }
+      at(DT_BMD, b - 1) = 0.0f;   // the next wave's cell: added on its own
+      bf[w] = acc;
+      bj[w] = acc * dd(a);
+      gf[w] = open;
+      gj[w] = open && dd(a) > 0.0;
+      float *edge = h_dconst + kDecEdge + w * 4;
+      edge[0] = (float)(b < n ? tr_prob(TR_MDIN, b) : 0.0);
+      edge[1] = (float)dd(b);
+      edge[2] = (float)(a > 0 ? tr_prob(TR_DMIN, a) : 0.0);
+      edge[3] = (float)(a > 0 ? dd(a) : 0.0);
+    }
+    auto cst = [&](int t, int w, int j) -> float & { return h_dconst[(t * kMaxDecWaves + w) * kMaxDecWaves + j]; };
+    for (int w = 0; w < dw; w++)
+      for (int j = 0; j < dw; j++) {
+        double f = 0.0, fprev = 0.0, bk = 0.0, bnext = 0.0;
+        bool g = false, gnext = false;
+        if (j < w) {       // wave j's passed value through waves j+1 .. w-1 into wave w
+          f = 1.0;
+          for (int m = j + 1; m < w; m++) f *= pj[m];
+        }
+        if (j < w - 1) {   // ... into wave w-1 and through it to its last delete cell
+          fprev = fl[w - 1];
+          for (int m = j + 1; m < w - 1; m++) fprev *= pj[m];
+        }
+        if (j > w) {
+          bk = 1.0;
+          g = true;
+          for (int m = w + 1; m < j; m++) {
+            bk *= bj[m];
+            g = g && gj[m];
+          }
+        }
+        if (j > w + 1) {
+          bnext = bf[w + 1];
+          gnext = gf[w + 1];
+          for (int m = w + 2; m < j; m++) {
+            bnext *= bj[m];
+            gnext = gnext && gj[m];
+          }
+        }
+        cst(DC_F, w, j) = (float)f;
+        cst(DC_FL, w, j) = (float)fprev;
+        cst(DC_B, w, j) = (float)bk;
+        cst(DC_BN, w, j) = (float)bnext;
+        cst(DC_GB, w, j) = g ? 0.0f : -INFINITY;
+        cst(DC_GN, w, j) = gnext ? 0.0f : -INFINITY;
+      }
+  }
+  int gated = 0;
+  for (int c = 0; c + 1 < M; c++)
+    for (int k = 0; k < 7; k++) gated |= !((float)d->trans[(size_t)c * 7 + k] > 0.0f);
+
   hipError_t e = hipMalloc(&p->dmem, total * sizeof(uint32_t));
   if (e != hipSuccess) {
     delete p;
@@ -486,6 +615,12 @@ int hmm_profile_upload(const hmm_profile_desc *d, hmm_stream stream, hmm_profile
   dv.v32_tr = dv.v32_emit + n_w32emit;
   dv.f_emit = (const float *)(dv.v32_tr + n_w32tr);
   dv.f_tr = dv.f_emit + n_w32emit;
+  dv.dec_qw = dqw;
+  dv.dec_w = dw;
+  dv.dec_gated = gated;
+  dv.d_emit = own_demit ? dv.f_tr + n_ftr : dv.f_emit;
+  dv.d_tr = dv.f_tr + n_ftr + n_demit;
+  dv.d_const = dv.d_tr + n_dtr;
   *out = p;
   return HMM_OK;
 }
@@ -1097,20 +1232,23 @@ int decode_impl(const hmm_profile *p, hmm_db *db, const uint8_t *flags, uint8_t 
   if (!p || !db || !out) return fail(HMM_EINVAL, "NULL profile, db or out");
   if (!out->dom || !out->n_dom) return fail(HMM_EINVAL, "NULL dom or n_dom");
   if (out->max_dom < 0) return fail(HMM_EINVAL, "max_dom = %d", out->max_dom);
-  // one scratch slot per resident wave, four per workgroup
-  const int64_t slot_dw = decode_slot_dw(p->dev.Q32, db->max_len);
+  // one scratch slot per resident team; teams of one wave come four to a block
+  const int64_t slot_dw = decode_slot_dw(p->dev.dec_qw, p->dev.dec_w, db->max_len);
   const size_t slot_bytes = (size_t)slot_dw * 4;
   const size_t budget = fixed ? kStaticDecodeBytes : kDecodeScratchMax;
-  int64_t nslots = decode_max_waves(p->dev);
-  nslots = std::min<int64_t>(nslots, (int64_t)(budget / slot_bytes));
-  nslots = std::min<int64_t>(nslots, (db->n + 3) / 4 * 4);
-  nslots = nslots / 4 * 4;
-  if (db->n > 0 && nslots < 4) {
+  // What is accepted: four slots of one wave per target must fit (a team's slot
+  // is at most a few per cent larger).
+  const size_t wave_bytes = (size_t)decode_slot_dw(p->dev.Q32, 1, db->max_len) * 4;
+  if (db->n > 0 && budget / wave_bytes < 4) {
     if (fixed)
       return fail(HMM_ERANGE, "hmm_decode_static: 4 waves of %zu bytes (M = %d, longest target %d) exceed the "
-                  "%zu-byte static scratch", slot_bytes, p->dev.M, db->max_len, kStaticDecodeBytes);
-    return fail(HMM_ENOMEM, "decode scratch: %zu bytes per wave exceed the budget", slot_bytes);
+                  "%zu-byte static scratch", wave_bytes, p->dev.M, db->max_len, kStaticDecodeBytes);
+    return fail(HMM_ENOMEM, "decode scratch: %zu bytes per wave exceed the budget", wave_bytes);
   }
+  int64_t nslots = decode_max_teams(p->dev);
+  nslots = std::min<int64_t>(nslots, (int64_t)(budget / slot_bytes));
+  nslots = std::min<int64_t>(nslots, (db->n + 3) / 4 * 4);
+  if (p->dev.dec_w == 1) nslots = nslots / 4 * 4;
   float *base = nullptr;
   if (fixed && db->n > 0) HIP_TRY(static_decode_scratch(&base), "hipGetSymbolAddress(scratch)");
   hipStream_t s = (hipStream_t)stream;

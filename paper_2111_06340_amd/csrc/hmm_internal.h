@@ -67,8 +67,56 @@ struct DevProfile {
   // plane TR_EXIT: exit weight g_c of cell c (see hmm_profile_upload), so
   // that a row's E = sum_c M_c g_c
   const float *f_tr;
+  // Decoding: teams of dec_w waves, dec_qw cells per lane and wave; cell of plane
+  // p (= wave * dec_qw + vector) and lane l: ((p / dec_qw) * 64 + l) * dec_qw + p % dec_qw.
+  int32_t dec_qw, dec_w;
+  int32_t dec_gated;            // 1: some transition inside the profile has probability 0
+  const float *d_emit;          // [20][2][dec_w dec_qw][64] odds, as f_emit
+  const float *d_tr;            // [DT_N][dec_w dec_qw][64]
+  const float *d_const;         // [kDecConst]
 };
 enum { TR_PRE = TR_N, TR_SUF = TR_N + 1, TR_EXIT = TR_N + 2 };
+
+// Planes of the decoding's transitions: 0 .. TR_N-1 as in TR_* ("into" form),
+// then
+//   DT_EXIT: exit weights; DT_PRE: prod_{j<=q} DDIN over the lane's cells;
+//   DT_FC: the factor from the value entering the wave's first delete cell to
+//     this delete cell;
+//   DT_MMO .. DT_DDO: the transitions out of the cell's node into the next one;
+//   DT_SUF: the factor from the next lane's first delete cell to this one in the
+//     Backward direction; DT_BMD: M->D times the factor from the value entering
+//     the wave's last delete cell to the next cell;
+//   DT_GSUF, DT_GC: 0 where the factor of DT_SUF, resp. of the value entering the
+//     wave's last delete cell, has no zero transition, else -inf;
+//   DT_PAD: 0 for the profile's cells, -inf past them.
+enum {
+  DT_EXIT = TR_N, DT_PRE, DT_FC, DT_MMO, DT_IMO, DT_DMO, DT_MDO, DT_DDO, DT_SUF, DT_BMD, DT_GSUF, DT_GC, DT_PAD, DT_N
+};
+// Constant tables [DC_N][wave][published by wave j]: coefficients of what wave j
+// passes on in wave w's entering value (DC_F, DC_B; max-plus DC_GB), in the last
+// delete cell of wave w - 1 (DC_FL) and in the first of wave w + 1 (DC_BN, DC_GN).
+// Then, per wave: M->D and D->D out of its last cell, D->M and D->D into its first.
+constexpr int kMaxDecWaves = 4;
+enum { DC_F = 0, DC_FL, DC_B, DC_BN, DC_GB, DC_GN, DC_N };
+constexpr int kDecEdge = DC_N * kMaxDecWaves * kMaxDecWaves;
+constexpr int kDecConst = kDecEdge + kMaxDecWaves * 4;
+// Waves per SIMD of a decoding instance: as many as its registers allow.
+constexpr int decode_waves_per_simd(int qw, int w, bool gated) {
+  return qw == 1 ? 4 : qw == 2 ? 3 : qw <= (gated ? 4 : 6) ? 2 : 1;
+}
+// The decoding instance of a profile of q vectors per lane: the smallest that
+// holds it.
+inline bool decode_split(int q, int *qw, int *w) {
+  static const int list[][2] = {{1, 1}, {2, 1}, {3, 1}, {4, 1}, {5, 1}, {3, 2}, {4, 2}, {5, 2}, {6, 2}, {4, 4},
+                                {5, 4}, {6, 4}, {7, 4}, {8, 4}, {10, 4}, {12, 4}};
+  for (const auto &e : list)
+    if (e[0] * e[1] >= q) {
+      *qw = e[0];
+      *w = e[1];
+      return true;
+    }
+  return false;
+}
 
 // Counters in the database scratch (device int32).
 enum {
@@ -129,23 +177,24 @@ struct DevDecode {
   int32_t sel_mask;             // decode targets with (flags & mask) == mask
   float rt1, rt2;               // region thresholds on the core posterior
   float *scratch;               // nslots * slot_dw floats
-  int64_t slot_dw;              // dwords per wave slot
-  int32_t nslots;               // waves of the decode launch (one slot each)
+  int64_t slot_dw;              // dwords per team slot
+  int32_t nslots;               // teams of the decode launch (one slot each)
 };
 
-// Dwords of one decode slot for vectors-per-lane Q and targets up to max_len:
-//   kept Forward rows [max_len][2][Q][64], their specials [max_len][8],
-//   regions [max_len / 2 + 1][8], traceback codes [max_len][ceil(Q/8)][64].
-inline int64_t decode_slot_dw(int Q, int max_len) {
-  const int64_t nb = (Q + 7) / 8;
-  const int64_t dw = (int64_t)max_len * (2 * Q * 64 + 8 + 4 + nb * 64) + 8;
+// Dwords of one decode slot for teams of w waves of qw cells per lane and
+// targets up to max_len: kept Forward rows [max_len][2][w qw][64], their
+// specials [max_len][8], regions [max_len / 2 + 1][8], traceback codes
+// [max_len][w][ceil(qw/8)][64].
+inline int64_t decode_slot_dw(int qw, int w, int max_len) {
+  const int64_t nb = (qw + 7) / 8;
+  const int64_t dw = (int64_t)max_len * (2 * qw * w * 64 + 8 + 4 + w * nb * 64) + 8;
   return (dw + 63) / 64 * 64;
 }
 
-// Largest number of waves of the decode kernel of profile p resident at once.
-int decode_max_waves(const DevProfile &p);
+// Largest number of teams of the decode kernel of profile p resident at once.
+int decode_max_teams(const DevProfile &p);
 
-// Enqueue the decode of the selected targets on `stream` (d.nslots waves).
+// Enqueue the decode of the selected targets on `stream` (d.nslots teams).
 hipError_t launch_decode(const DevProfile &p, const DevDb &db, const DevDecode &d, hipStream_t stream);
 
 // Bytes of the decode scratch held in a file-scope device array, for the

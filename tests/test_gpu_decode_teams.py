@@ -1,0 +1,44 @@
+"""Decoding instances at their edges: profile sizes on both sides of every change
+of vectors per lane or waves per target, with random transitions at every node
+(a value taken from the wrong neighbour at a lane's, or a wave's, edge changes
+the posteriors) and with zero-probability transitions (the gated instances)."""
+import pytest
+
+from conftest import random_profile
+from synth import gen
+from test_gpu_decode import _check_selection, compare_decode, gpu, run  # noqa: F401
+from test_gpu_parity import _ragged_db, announce
+from test_oracle_decode import _zero_transition_profile
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [192, 193, 257, 320, 321, 384, 385, 512, 513, 640, 641, 768, 769, 1024, 1025, 1280, 1281, 1536, 1537, 1792, 1793,
+         2048, 2049, 2560, 2561, 3072]
+
+
+@pytest.mark.parametrize("M", SIZES)
+def test_random_transitions(M):
+    prof = random_profile(M, 3000 + M, alpha=0.3, talpha=0.6)
+    res_, off = _ragged_db(prof, M, lengths=[M + M // 4, 2, 130, 1, 65], homolog_every=2)
+    res, g = run(prof, res_, off, (0.0, 0.0, 0.0), (1.0, 1.0, 1.0), decode_all=True)
+    st = compare_decode(prof, res_, off, g, _check_selection(res, g, True), f"teams M={M}")
+    announce(f"decode teams M={M}: {st}")
+    assert st["regions"] >= 1
+
+
+@pytest.mark.parametrize("M", [128, 320, 512, 641, 1000, 1281, 2100])
+def test_zero_transitions(M):
+    prof = _zero_transition_profile(M, 70 + M)
+    res_, off = _ragged_db(prof, M, lengths=[M + M // 4, 3, 129], homolog_every=1)
+    res, g = run(prof, res_, off, (0.0, 0.0, 0.0), (1.0, 1.0, 1.0), decode_all=True)
+    st = compare_decode(prof, res_, off, g, _check_selection(res, g, True), f"zero transitions M={M}")
+    announce(f"decode teams, zero transitions M={M}: {st}")
+
+
+def test_regions_at_both_ends():
+    """A region that starts at residue 1 and one that ends at the last, in targets of one and of several windows."""
+    prof = gen.make_profile(60, 5)
+    res_, off = _ragged_db(prof, 9, lengths=[60, 63, 64, 65, 128, 129], homolog_every=1)
+    res, g = run(prof, res_, off, (0.0, 0.0, 0.0), (1.0, 1.0, 1.0), decode_all=True)
+    compare_decode(prof, res_, off, g, _check_selection(res, g, True), "ends")
+    assert any(d["s"] == 1 for d in g["doms"])
