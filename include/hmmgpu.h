@@ -11,7 +11,7 @@
  *
  *   MSV      uint8 saturating, multi-segment ungapped, on every target
  *   Viterbi  int16 saturating, gapped local, on MSV survivors
- *            (targets that saturate int16 are rescored exactly in int32)
+ *            (targets that pass the int16 range get their exact int32 score)
  *   Forward  fp32 sum over all paths, on Viterbi survivors
  *
  * The model, its integer score systems and the filter cutoffs are not given
@@ -60,7 +60,7 @@ extern "C" {
 #define HMM_MSV_OVF 0x02  /* MSV saturated uint8; msv = 255 */
 #define HMM_VIT_RAN 0x04  /* Viterbi was computed */
 #define HMM_VIT_PASS 0x08 /* passed the Viterbi filter (always set when Viterbi overflowed) */
-#define HMM_VIT_OVF 0x10  /* Viterbi saturated int16; vit holds the exact int32 rescore */
+#define HMM_VIT_OVF 0x10  /* Viterbi passed the int16 range; vit holds the exact int32 score */
 #define HMM_FWD_RAN 0x20  /* Forward was computed */
 #define HMM_FWD_PASS 0x40 /* Forward score passed the F3 cutoff (set for every Forward target when F3 >= 1) */
 #define HMM_BIAS_PASS 0x80 /* passed the composition-bias filter (only set when the filter is on) */
@@ -106,8 +106,8 @@ typedef struct {
  * database order.  Written asynchronously on the search stream; valid after
  * that stream synchronises.
  *   msv[i]    MSV raw score 0..255 (255 = overflow)
- *   vit[i]    Viterbi score in 1/500-bit units (exact int32 rescore after an
- *             int16 overflow); INT32_MIN when Viterbi did not run
+ *   vit[i]    Viterbi score in 1/500-bit units (the exact int32 score after
+ *             an int16 overflow); INT32_MIN when Viterbi did not run
  *   fwd[i]    Forward score in nats, raw (before the null-model correction);
  *             NaN when Forward did not run
  *   flags[i]  HMM_* flag bits
@@ -169,11 +169,13 @@ int hmm_db_share(const hmm_db *db, hmm_db **out);
  * MSV survivors, int32 rescore of int16-overflowed targets, Forward on
  * Viterbi survivors.  Enqueued on `stream` without host synchronisation
  * (except when the cutoffs change, see below); allocates nothing.  The
- * search runs pipelined in chunks of the database (hmm_db_pipeline): the
- * MSV kernels run on `stream`; Viterbi and Forward of each chunk on a
- * stream owned by the database handle and the int32 rescore on another,
- * forked from `stream` and joined back before the search ends, so all of
- * the search's work is ordered on `stream`.
+ * search runs on `stream`; one that is pipelined in chunks of the database
+ * (hmm_db_pipeline) runs the MSV kernels there and Viterbi and Forward of
+ * each chunk on a stream owned by the database handle.  That search, and one
+ * by a profile whose int16 overflows the Viterbi kernel does not score exactly
+ * by itself, runs the int32 rescore on another such stream, beside Forward.
+ * These streams are forked from `stream` and joined back before the search
+ * ends, so all of the search's work is ordered on `stream`.
  * Searches on one database are serialised by the library (a search on a
  * second stream waits for the previous one on the GPU).  Changing the
  * cutoffs or the profile between searches on a database rebuilds a small
@@ -339,8 +341,8 @@ int hmm_db_stage_timing(hmm_db *db, int32_t capacity);
 /* Stage durations (ms) of the recorded searches, oldest first:
  * out_ms[4*i + s] for search i and stage s = MSV, Viterbi int16, int32
  * rescore, Forward (each including its small list/counter kernels).  The
- * rescore and Forward run concurrently (the rescore on a stream internal to
- * the database, forked from and joined back into the search stream): both
+ * rescore and Forward may run concurrently (the rescore on a stream internal
+ * to the database, forked from and joined back into the search stream): both
  * are timed from the end of the int16 Viterbi stage, the rescore to its own
  * end and Forward to the end of both, so Forward's figure is the time the
  * two together add to the search.  When the three stages after MSV run as
@@ -373,7 +375,7 @@ int hmm_db_pipeline(hmm_db *db, int32_t chunks, int32_t *current);
 
 /* Tuning hook: how a search on this handle runs the stages after MSV.
  * mode 1: one kernel per stage (int16 Viterbi over every MSV survivor, then
- * the int32 rescore of its overflows beside Forward over its passes).
+ * the int32 rescore of the overflows it left and Forward over its passes).
  * mode 2: for profiles of at most 384 nodes, one kernel in which a wave
  * takes each MSV survivor through its Viterbi, rescore (if it overflowed)
  * and Forward (if it passed) before its next target, so that no stage

@@ -113,29 +113,7 @@ __device__ __forceinline__ float readlane_f(float v, int l) {
 // Memory written by other lanes of this wave becomes visible to its loads.
 __device__ __forceinline__ void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); }
 
-// Independent lane scans advance together, a step of each in turn: a step waits
-// eight clocks for the one before it, and two wait states separate a VALU write
-// from a DPP read of it; the other scans' steps fill both.  Sums end in lane 63
-// (wave_sum_lane63), the affine scan is affine_scan_fused, the maximum is
-// inclusive (a lane without a source keeps its value).
-__device__ __forceinline__ void scan_sum_affine(float &s, float &a, const float (&ps)[6]) {
-  asm volatile(
-      "s_nop 1\n\t"
-      "v_add_f32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %1, %1, %2 row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\ts_nop 0\n\t"
-      "v_add_f32_dpp %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %1, %1, %3 row_shr:2 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\ts_nop 0\n\t"
-      "v_add_f32_dpp %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %1, %1, %4 row_shr:4 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\ts_nop 0\n\t"
-      "v_add_f32_dpp %0, %0, %0 row_shr:8 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %1, %1, %5 row_shr:8 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\ts_nop 0\n\t"
-      "v_add_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
-      "v_fmac_f32_dpp %1, %1, %6 row_bcast:15 row_mask:0xa bank_mask:0xf\n\ts_nop 0\n\t"
-      "v_add_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
-      "v_fmac_f32_dpp %1, %1, %7 row_bcast:31 row_mask:0xc bank_mask:0xf\n\ts_nop 1"
-      : "+v"(s), "+v"(a)
-      : "v"(ps[0]), "v"(ps[1]), "v"(ps[2]), "v"(ps[3]), "v"(ps[4]), "v"(ps[5]));
-}
+// The same with two sums and a maximum.
 __device__ __forceinline__ void scan_sums_affine_max(float &s, float &t, float &a, const float (&ps)[6], float &m) {
 #define HMM_STEP(P, CTRL)                                  \
   "v_add_f32_dpp %0, %0, %0 " CTRL "\n\t"                  \

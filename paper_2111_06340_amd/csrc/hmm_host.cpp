@@ -602,6 +602,18 @@ int hmm_profile_upload(const hmm_profile_desc *d, hmm_stream stream, hmm_profile
     dv.dm_max16 = std::max(dv.dm_max16, lo16(tr_cell(TR_DMIN, c)));
     dv.dm_max32 = std::max(dv.dm_max32, w32(tr_cell(TR_DMIN, c)));
   }
+  // Re-basing brings the largest value (at most 32766) down to 8000 and needs
+  // room above that for a row's growth.  A profile whose rescore has a
+  // cooperative instance leaves its overflows to that: it takes them with two to
+  // four waves per target beside Forward, where the one wave of the int16 kernel
+  // would take 2.7 us a row (M = 2,500 x 300,000 targets with 0.2 % homologs:
+  // Viterbi 4.0 ms, then Forward 3.2 beside the rescore 5.4, against 7.0 and 3.2
+  // re-based; 15.8 against 16.4 ms a search).
+  int msc_min = 0, mi_min = 0;
+  for (int16_t v : p->msc16) msc_min = std::min(msc_min, (int)v);
+  for (int k = 1; k < M; k++) mi_min = std::min(mi_min, t16(k, 1));
+  dv.s_max = p->s_max;
+  dv.rebase_w = p->s_max <= 12000 && !coop_instance(Q32) ? -msc_min - mi_min : 1 << 20;
   dv.entry_p = (float)(2.0 / ((double)M * ((double)M + 1.0)));
   for (int a = 0; a < kAlpha; a++) {
     double m = 0.0;
@@ -1067,6 +1079,12 @@ int hmm_db_info(const hmm_db *db, int64_t *n_seqs, int64_t *n_residues, int32_t 
 // by its Forward), is the faster one.
 static int fuse_tail(int mode, const hmm_thresholds &t) { return mode == 2 || (mode == 3 && t.F2 >= 1.0); }
 
+// Whether the int16 Viterbi re-bases every target of the database (its test for
+// the longest one), so that the int32 rescore has next to nothing to do.
+static bool rescore_apart(const hmm_profile *p, const hmm_db *db) {
+  return move16_of(std::max(db->max_len, 1)) + p->entry16 < kNeg16 + p->dev.rebase_w;
+}
+
 // Every transition score is <= 0 and a path emits at most once per residue,
 // so no Viterbi value of a target of length L exceeds L * s_max.  The int32
 // rescore is exact while that stays below 2^29 (its delete floor drops
@@ -1105,7 +1123,7 @@ int hmm_search(const hmm_profile *p, hmm_db *db, const hmm_thresholds *t, const 
     db->lp_F[2] = t->F3;
   }
   DevOut o{out->msv,  out->vit,       out->fwd, out->flags, out->counts,
-           out->bias, t->bias_filter, fuse_tail(db->fused_tail, *t)};
+           out->bias, t->bias_filter, fuse_tail(db->fused_tail, *t), rescore_apart(p, db)};
   hipEvent_t *ev = nullptr;
   if (db->tcap > 0) ev = &db->tev[(size_t)(db->trec++ % db->tcap) * 5];
   DevDb chunk[kMaxChunks];
@@ -1169,7 +1187,7 @@ int hmm_search_group(const hmm_profile *const *p, hmm_db *const *db, const hmm_t
     D[i] = chunk_of(d->dev, 0, d->n, 0);
     D[i].prio_by_len = 1;
     O[i] = DevOut{out[i].msv,    out[i].vit,  out[i].fwd,        out[i].flags,
-                  out[i].counts, out[i].bias, t[i].bias_filter, fuse_tail(d->fused_tail, t[i])};
+                  out[i].counts, out[i].bias, t[i].bias_filter, fuse_tail(d->fused_tail, t[i]), rescore_apart(p[i], d)};
     Y[i] = &d->sync;
   }
   HIP_TRY(launch_search_group(P.data(), D.data(), O.data(), n, s, Y.data()), "kernel launch");

@@ -48,6 +48,10 @@ struct DevProfile {
   // minus infinity when M = 1): a delete value d with d + dm_max <= the
   // B->M entry value can no longer change any match cell.
   int32_t dm_max16, dm_max32;
+  // Re-basing of the int16 Viterbi: the largest emission score, and W (the least
+  // distance of xBe from the int16 floor; so large that no target qualifies
+  // where the emission scores leave no room).
+  int32_t s_max, rebase_w;
   float entry_p;                // 2/(M(M+1))
   float bias_r[kAlpha];         // composition-bias filter: mean match emission / background
   // MSV table, packed fp16 scores E = BIAS8 - COST8 times 2^-11 (padding
@@ -122,6 +126,7 @@ inline bool decode_split(int q, int *qw, int *w) {
 enum {
   CNT_VIT = 0, CNT_OVF, CNT_FWD, CNT_FWD_PASS,
   CNT_DEC, CNT_NDOM,   // posterior decoding: list size, domains found
+  CNT_OVF_EXACT,       // int16 overflows scored exactly by re-basing (not in CNT_OVF)
   CNT_LISTS = 8,       // the counters above
   // work counters of the stages, kWorkLanes of them each, kWorkStride apart
   CNT_WORK = 32
@@ -163,6 +168,7 @@ struct DevOut {
   float *bias;                  // optional bias scores
   int32_t bias_filter;          // 1: composition-bias filter between MSV and Viterbi
   int32_t fused_tail;           // 1: the stages after MSV as one kernel where an instance exists
+  int32_t rescore_apart;        // 1: the int32 rescore on its own stream, beside Forward
 };
 
 // Posterior decoding (hmm_decode): outputs and per-wave scratch.
@@ -215,16 +221,16 @@ hipError_t launch_vit32_coop(const DevProfile &p, const DevDb &db, const DevOut 
 // A search runs in up to kMaxChunks chunks of the length-sorted database
 // (contiguous ranges of about equal residue counts), pipelined: the MSV
 // kernels of the chunks run back to back on the search stream, and the rest
-// of each chunk's cascade (Viterbi, then Forward, with the int32 rescore
-// beside it) on a second stream as soon as the chunk's MSV is done, so it
-// overlaps the next chunk's MSV.  Each chunk has its own counter block and
+// of each chunk's cascade (Viterbi, the int32 rescore, Forward) on a second
+// stream as soon as the chunk's MSV is done, so it overlaps the next chunk's
+// MSV.  A search of one chunk needs no second stream.  Each chunk has its own counter block and
 // keeps its survivor lists inside its own index range.
 constexpr int kMaxChunks = 8;
 
 // Streams and events that order one database handle's searches.
 struct SearchSync {
   hipStream_t tail = nullptr;           // Viterbi and Forward of the chunks
-  hipStream_t aux = nullptr;            // int32 rescore, beside Forward
+  hipStream_t aux = nullptr;            // int32 rescore beside Forward (DevOut::rescore_apart)
   hipEvent_t msv_done[kMaxChunks] = {}; // recorded on the search stream
   hipEvent_t vit_done[kMaxChunks] = {}; // recorded on tail
   hipEvent_t aux_done = nullptr, tail_done = nullptr;
@@ -248,11 +254,11 @@ inline DevDb chunk_of(const DevDb &d, int64_t a, int64_t b, int k) {
 }
 
 // Enqueue the whole cascade of the chunks chunk[0..nchunks) on `stream`;
-// all of its work is joined back into `stream` before the final counter
-// export (the sum over the chunks' counter blocks, which start at
-// chunk[0].counters).  When `ev` is non-null, ev[0..4] are recorded at the
-// start and after the last MSV (search stream), after the last Viterbi
-// (tail), after the last rescore (aux) and at the end (search stream).
+// all of its work is joined back into `stream`.  The last kernel writes the
+// results in caller order and the counts (the sum over the chunks' counter
+// blocks, which start at chunk[0].counters).  When `ev` is non-null, ev[0..4]
+// are recorded at the start, after the last MSV, after the last Viterbi, after
+// the last rescore and at the end, each on the stream that ran it.
 hipError_t launch_search(const DevProfile &p, const DevDb *chunk, int nchunks, const DevOut &out,
                          hipStream_t stream, const SearchSync &sync, hipEvent_t *ev);
 

@@ -152,6 +152,33 @@ __global__ void reset_ovf(int32_t *c) {
 // the lazy propagation stops as soon as the chains that cross a slot
 // boundary fall to the floor, instead of running every chain to its end.
 
+// Overflow without a second pass: where the scores allow it the values are
+// re-based instead of saturating.  Stored values are the true ones less `off`.
+// When a match or insert value passes RL = 32766 - s_max (s_max: the largest
+// emission score, so one row cannot take a value from RL to 32767), the largest
+// is brought down to kRebaseTo and off grows by the difference; the result is
+// then the exact int32 score, and the overflow flag says that some true value
+// reached 32767.  Values that fall below the stored floor F = -32768 are clipped
+// there, which changes nothing while
+//   xBe - off >= F + W,  W = - min msc - min MI     (*)
+// since then no match value (at least xBe + msc) is clipped, a clipped insert
+// value lies below M + MI, the insert maximum's other term, and below xBe where
+// it enters a match maximum, and the delete floor lies above F.  xBe never
+// decreases, so (*) is tested with the first row's (where it fails the target is
+// not re-based) and, with the xBe that the latest row used, at every re-basing
+// (where it fails the target goes to the int32 rescore, as every overflow of a
+// target that is not re-based does).
+//
+// Measured with every overflow left to the rescore, and re-based: M = 734 x 1M
+// targets (1 % homologs), Viterbi 2.50 and 2.74 ms and the rescore 1.68 ms and
+// none, 11.4 and 10.6 ms a search; M = 256 x 300,000, Viterbi 0.43 and 0.64 ms,
+// 1,810 and 1,700 us a search.
+constexpr int kRebaseTo = 8000;
+// Instances that re-base: the profiles with a one-wave rescore (up to 768
+// nodes; the others' rescore is cooperative).
+template <int Q>
+constexpr bool kRebase16 = Q <= 6;
+
 // Threads per block of the Viterbi kernel.  Large instances run one wave per
 // SIMD (4 waves per block): each wave may then use the whole register file,
 // architectural and accumulation registers, and spills go to accumulation
@@ -166,13 +193,14 @@ constexpr int kThreads16 = Q >= 16 ? 256 : 512;
 template <int Q>
 constexpr bool kTrLds16 = Q == 16 || Q == 20;
 template <int Q>
-constexpr int kMinWaves16 = kTrLds16<Q> ? 2 : 1;
+constexpr int kMinWaves16 = kTrLds16<Q> ? 2 : Q == 6 ? 4 : 1;
 // Threads per block of the one-wave rescore and Forward kernels.
 constexpr int kThreads32 = 512;
 
 struct VitResult {
   int raw;
-  bool ovf;
+  bool ovf;    // a true match or insert value reached 32767
+  bool redo;   // ... and raw is not the exact score
 };
 
 
@@ -186,13 +214,27 @@ __device__ __forceinline__ VitResult vit16_target(const uint32_t *__restrict__ e
   uint32_t accM = kNegNeg, accI = kNegNeg;
   const int mv = lp.move16, ej = P.ej16, entry = P.entry16;
   int xJt = kNeg16;
-  int xB = sat16(mv);
-  uint32_t xbe2 = splat16(sat16(xB + entry));
+  int xbt = mv + entry;   // the true xBe
+  uint32_t xbe2 = splat16(sat16(xbt));
   auto floor_of = [&](int xbe) { return splat16(min(xbe - P.dm_max16, 32767)); };
-  uint32_t tau2 = floor_of(sat16(xB + entry));
-  int T = min(-ej + 1, 32767);
-  uint32_t tm1 = splat16(T - 1);
-  bool ovf = false;
+  uint32_t tau2 = floor_of(sat16(mv + entry));
+  const bool reb = kRebase16<Q> && mv + entry >= kNeg16 + P.rebase_w;
+  const int RL = reb ? 32766 - P.s_max : 32766;
+  const uint32_t rl2 = splat16(RL);
+  int off = 0, top = 0;   // top: the largest true value at a re-basing
+  // trigger: some accM > tm1, or some accI > RL, i.e. accI + iadj > tm1
+  uint32_t tm1 = splat16(min(-ej, 32766));
+  uint32_t iadj = reb ? splat16(min(-ej, 32766) - RL) : kNegNeg;
+  // xJ, xB and the trigger from the largest (stored) match value m so far
+  auto settle = [&](int m) {
+    xJt = max(xJt, m + off + ej);
+    xbt = max(mv, xJt + mv) + entry;
+    xbe2 = splat16(sat16(xbt - off));
+    tau2 = floor_of(sat16(xbt - off));
+    const int t1 = max(min(max(xJt, 0) - ej - off, 32766), kNeg16);
+    tm1 = splat16(t1);
+    if (reb) iadj = splat16(max(t1 - RL, kNeg16));
+  };
   auto load = [&](uint32_t(&e)[2 * Q], int a) {
     const uint32_t *er = emit + a * (2 * Q * kWave);
 #pragma unroll
@@ -202,9 +244,9 @@ __device__ __forceinline__ VitResult vit16_target(const uint32_t *__restrict__ e
     // LDS planes: an offset the compiler cannot see through keeps their
     // reads inside the row (loop-invariant reads would be hoisted back
     // into registers)
-    int off = 0;
-    if (TRL) asm volatile("" : "+v"(off));
-    auto trv = [&](int k, int q) -> uint32_t { return TRL ? ltr[off + (k * Q + q) * kWave] : tr[k][q]; };
+    int lofs = 0;
+    if (TRL) asm volatile("" : "+v"(lofs));
+    auto trv = [&](int k, int q) -> uint32_t { return TRL ? ltr[lofs + (k * Q + q) * kWave] : tr[k][q]; };
     const uint32_t msh = slot_up16(M[Q - 1]);
     const uint32_t ish = slot_up16(I[Q - 1]);
     const uint32_t dsh = slot_up16(D[Q - 1]);
@@ -253,29 +295,54 @@ __device__ __forceinline__ VitResult vit16_target(const uint32_t *__restrict__ e
         if (!moved) break;
       }
     }
-    if (__builtin_expect(any_lane(i16_max(accM, tm1) != tm1), 0)) {
+    const uint32_t acc = kRebase16<Q> ? i16_max(accM, i16_adds(accI, iadj)) : accM;
+    if (__builtin_expect(any_lane(i16_max(acc, tm1) != tm1), 0)) {
       const int m = wave_max_i32(hmax16(accM));
-      if (m >= 32767) return true;
-      xJt = max(xJt, sat16(m + ej));
-      xB = max(sat16(mv), sat16(xJt + mv));
-      xbe2 = splat16(sat16(xB + entry));
-      tau2 = floor_of(sat16(xB + entry));
-      T = min(max(xJt, 0) - ej + 1, 32767);
-      tm1 = splat16(T - 1);
+      if (m > RL || (kRebase16<Q> && any_lane(i16_max(accI, rl2) != rl2))) return true;
+      settle(m);
     }
     return false;
   };
   uint32_t ea[2 * Q], eb[2 * Q];
-  int stop;
-  ovf = drive_rows(x, L, 0, 0, stop, lane, ea, eb, load, row);
-  if (!ovf) ovf = any_lane(hmax16(accI) >= 32767);
   VitResult res;
-  res.ovf = ovf;
-  if (ovf) {
+  res.redo = false;
+  for (int r = 0; r < L;) {
+    int stop = 0;
+    if (!drive_rows(x, L, r, 0, stop, lane, ea, eb, load, row)) break;
+    // a value above RL (32766 without re-basing: an overflow)
+    if (!reb) {
+      res.redo = true;
+      break;
+    }
+    const int m = wave_max_i32(hmax16(accM));
+    const int hi = max(m, wave_max_i32(hmax16(accI))), sh = hi - kRebaseTo;
+    top = max(top, hi + off);
+    off += sh;
+    if (xbt - off < kNeg16 + P.rebase_w) {
+      res.redo = true;
+      break;
+    }
+    const uint32_t sh2 = splat16(sh);
+#pragma unroll
+    for (int q = 0; q < Q; q++) {
+      M[q] = i16_subs(M[q], sh2);
+      I[q] = i16_subs(I[q], sh2);
+      D[q] = i16_subs(D[q], sh2);
+    }
+    accM = i16_subs(accM, sh2);
+    accI = i16_subs(accI, sh2);
+    settle(m - sh);
+    r = stop + 1;
+  }
+  if (!res.redo && !reb) res.redo = any_lane(hmax16(accI) >= 32767);
+  if (res.redo) {
+    res.ovf = true;
     res.raw = 32767;
   } else {
-    const int m = wave_max_i32(hmax16(accM));
-    res.raw = sat16(sat16(m + ej) + mv);
+    const int m = wave_max_i32(hmax16(accM)) + off;
+    if (off > 0) top = max(top, max(m, wave_max_i32(hmax16(accI)) + off));
+    res.ovf = top >= 32767;
+    res.raw = res.ovf ? m + ej + mv : sat16(sat16(m + ej) + mv);
   }
   return res;
 }
@@ -315,7 +382,10 @@ __global__ void __launch_bounds__(kThreads16<Q>, kMinWaves16<Q>) vit16_kernel(De
         (uint8_t)(uni(db.flags_sorted[t]) | HMM_VIT_RAN | (pass ? HMM_VIT_PASS : 0) | (r.ovf ? HMM_VIT_OVF : 0));
     db.flags_sorted[t] = fl;
     out.vit[uni(db.perm[t])] = r.raw;
-    if (r.ovf) db.list_ovf[wave_fetch_add(&db.counters[CNT_OVF], 1)] = t;
+    if (r.redo)
+      db.list_ovf[wave_fetch_add(&db.counters[CNT_OVF], 1)] = t;
+    else if (r.ovf)
+      (void)wave_fetch_add(&db.counters[CNT_OVF_EXACT], 1);
     if (pass) db.list_fwd[wave_fetch_add(&db.counters[CNT_FWD], 1)] = t;
     idx = queue.next();
   }
@@ -535,10 +605,12 @@ __device__ __forceinline__ float fwd_target(const float *emit, const FwdRegs<Q> 
     D[0] = mul_up(M[Q - 1], TR(TR_MDIN, 0));
 #pragma unroll
     for (int q = 1; q < Q; q++) D[q] = fmaf(M[q - 1], TR(TR_MDIN, q), D[q - 1] * TR(TR_DDIN, q));
-    const float carry = lane_up_f(affine_scan_fused(D[Q - 1], pstep));
+    float chain = D[Q - 1];
+    scan_sum_affine(part, chain, pstep);
+    const float carry = lane_up_f(chain);
 #pragma unroll
     for (int q = 0; q < Q; q++) D[q] = fmaf(carry, TR(TR_N, q), D[q]);
-    const float E = wave_sum_fused(part);
+    const float E = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, part), 63));
     J = fmaf(J, loop, 0.5f * E);
     C = fmaf(C, loop, 0.5f * E);
     N = N * loop;
@@ -655,8 +727,8 @@ __global__ void __launch_bounds__(kThreadsTail<Q8>) tail_kernel(DevProfile P, De
     }
     const bool pass = r.ovf || r.raw >= lp.thr16;
     int vit = r.raw;
-    if (r.ovf) {
-      (void)wave_fetch_add(&db.counters[CNT_OVF], 1);
+    if (r.ovf) (void)wave_fetch_add(&db.counters[CNT_OVF_EXACT], 1);
+    if (r.redo) {
       int tr[TR_N][Q32];
       load_tr32<Q32>(P, ln, tr);
       vit = vit32_target<Q32>(e32, tr, P, x, L, lp, lane);
@@ -690,27 +762,25 @@ __global__ void clear_counters(int32_t *counters) {
   if (i < WORK_STAGES * kWorkLanes) c[CNT_WORK + i * kWorkStride] = 0;
 }
 
-__global__ void export_counts(const int32_t *c, int nblocks, int64_t *counts) {
-  if (threadIdx.x == 0) {
-    int64_t v[4] = {0, 0, 0, 0};
-    for (int k = 0; k < nblocks; k++) {
-      const int32_t *b = c + k * CNT_N;
-      v[0] += b[CNT_VIT];
-      v[1] += b[CNT_OVF];
-      v[2] += b[CNT_FWD];
-      v[3] += b[CNT_FWD_PASS];
-    }
-    for (int i = 0; i < 4; i++) counts[i] = v[i];
-  }
-}
-
 // Results in the caller's order, once every stage of a search is done: each
 // thread takes one caller index c and its sorted index iperm[c]; the flags
 // and MSV score come from the sorted arrays the stages wrote, and Viterbi
 // and Forward scores, written in caller order by those stages for the
 // targets they scored, get INT32_MIN and NaN where the stage did not run.
-// Reads of iperm and writes of every output are contiguous.
-__global__ void __launch_bounds__(256) results_kernel(DevDb db, DevOut out) {
+// Reads of iperm and writes of every output are contiguous.  The first block
+// also exports the counts (the sum over the chunks' counter blocks).
+__global__ void __launch_bounds__(256) results_kernel(DevDb db, DevOut out, int nblocks) {
+  if (blockIdx.x == 0 && threadIdx.x == 0 && out.counts) {
+    int64_t v[4] = {0, 0, 0, 0};
+    for (int k = 0; k < nblocks; k++) {
+      const int32_t *b = db.counters + k * CNT_N;
+      v[0] += b[CNT_VIT];
+      v[1] += b[CNT_OVF] + b[CNT_OVF_EXACT];
+      v[2] += b[CNT_FWD];
+      v[3] += b[CNT_FWD_PASS];
+    }
+    for (int i = 0; i < 4; i++) out.counts[i] = v[i];
+  }
   const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= db.n) return;
   const int t = db.iperm[c];
@@ -891,22 +961,27 @@ hipError_t launch_search(const DevProfile &P, const DevDb *chunk, int K, const D
       ok(launch_msv(&P, &chunk[k], &o, 1, s));
       if (o.bias_filter) ok(launch_bias(P, chunk[k], o, s));
     }
-    ok(hipEventRecord(y.msv_done[k], s));
+    if (K > 1) ok(hipEventRecord(y.msv_done[k], s));
   }
   mark(1, s);
   if (e != hipSuccess) return e;
   return launch_tail(P, chunk, K, o, s, y, ev);
 }
 
-// The rest of each chunk's cascade as soon as its MSV is done (event
-// y.msv_done[k] on the search stream).  An int16 overflow passes the
-// Viterbi filter whatever its exact score, so Forward needs nothing from
-// the rescore: the two run side by side.  With `o.fused_tail` and a profile
-// that has a fused instance, one kernel takes all three stages instead (the
-// rescore stream then has nothing to run).  The counts and the caller-order
-// results follow on the tail stream, whose end (y.tail_done) the search
-// stream waits for when `join` is set (a group of searches joins them all
-// at its end instead).
+// The rest of each chunk's cascade as soon as its MSV is done, then the counts
+// and the caller-order results.  A single search of one chunk runs it all on
+// the search stream; chunks, and the searches of a group, on the handle's tail
+// stream (event y.msv_done[k] on the search stream starts them, and the search
+// stream waits for y.tail_done when `join` is set; a group joins all of its
+// searches at its end).  With `o.fused_tail` and a profile that has a fused
+// instance, one kernel takes all three stages.  Otherwise the rescore runs
+// beside Forward on a stream of its own (an overflow passes the Viterbi filter
+// whatever its exact score, so Forward needs nothing from it).  Only a search
+// that keeps to the search stream and whose overflows are re-based (not
+// o.rescore_apart) runs it before Forward: there it has nothing to do in
+// ordinary searches, and an empty launch takes 4 us, a fork and join of streams
+// 10 to 20.  (In a group of 12 the searches' streams overlap each other: 10.04 ms
+// with the empty launches in line, 9.94 beside Forward.)
 hipError_t launch_tail(const DevProfile &P, const DevDb *chunk, int K, const DevOut &o, hipStream_t s,
                        const SearchSync &y, hipEvent_t *ev, bool join) {
   hipError_t e = hipSuccess;
@@ -918,35 +993,36 @@ hipError_t launch_tail(const DevProfile &P, const DevDb *chunk, int K, const Dev
     if (ev) ok(hipEventRecord(ev[i], st));
   };
   const bool fused = o.fused_tail && tail_fused_instance(P);
+  const bool own = K > 1 || !join;
+  const bool apart = (o.rescore_apart || own) && !fused;
+  const hipStream_t ts = own ? y.tail : s;
   for (int k = 0; k < K && e == hipSuccess; k++) {
     const bool any = chunk[k].n > 0;
     const DevDb &ck = chunk[k];
-    if (!ok(hipStreamWaitEvent(y.tail, y.msv_done[k], 0))) break;
-    if (any && !ok(fused ? dispatch_tail_fused(P, ck, o, y.tail) : dispatch_vit16(P, ck, o, y.tail))) break;
-    if (!ok(hipEventRecord(y.vit_done[k], y.tail))) break;
-    if (k == K - 1) mark(2, y.tail);
-    if (!ok(hipStreamWaitEvent(y.aux, y.vit_done[k], 0))) break;
+    if (own && !ok(hipStreamWaitEvent(ts, y.msv_done[k], 0))) break;
+    if (any && !ok(fused ? dispatch_tail_fused(P, ck, o, ts) : dispatch_vit16(P, ck, o, ts))) break;
+    if (k == K - 1) mark(2, ts);
+    if (apart) {
+      if (!ok(hipEventRecord(y.vit_done[k], ts)) || !ok(hipStreamWaitEvent(y.aux, y.vit_done[k], 0))) break;
+      if (any && !ok(dispatch_vit32(P, ck, o, y.aux))) break;
+    }
     if (fused) continue;
-    if (any && !ok(dispatch_vit32(P, ck, o, y.aux))) break;
-    if (any && !ok(dispatch_fwd(P, ck, o, y.tail))) break;
+    if (any && !apart && !ok(dispatch_vit32(P, ck, o, ts))) break;
+    if (k == K - 1 && !apart) mark(3, ts);
+    if (any && !ok(dispatch_fwd(P, ck, o, ts))) break;
   }
-  mark(3, y.aux);
-  if (ok(hipEventRecord(y.aux_done, y.aux))) ok(hipStreamWaitEvent(y.tail, y.aux_done, 0));
-  if (e == hipSuccess && o.counts) {
-    hipLaunchKernelGGL(export_counts, dim3(1), dim3(64), 0, y.tail, (const int32_t *)chunk[0].counters, K,
-                       o.counts);
-    ok(hipGetLastError());
-  }
+  if (apart || fused) mark(3, apart ? y.aux : ts);
+  if (apart && ok(hipEventRecord(y.aux_done, y.aux))) ok(hipStreamWaitEvent(ts, y.aux_done, 0));
   // chunk 0 starts at sorted index 0: its sorted arrays are the whole
   // database's
   DevDb all = chunk[0];
   all.n = 0;
   for (int k = 0; k < K; k++) all.n += chunk[k].n;
   if (e == hipSuccess && all.n > 0) {
-    hipLaunchKernelGGL(results_kernel, dim3((unsigned)((all.n + 255) / 256)), dim3(256), 0, y.tail, all, o);
+    hipLaunchKernelGGL(results_kernel, dim3((unsigned)((all.n + 255) / 256)), dim3(256), 0, ts, all, o, K);
     ok(hipGetLastError());
   }
-  if (ok(hipEventRecord(y.tail_done, y.tail)) && join) ok(hipStreamWaitEvent(s, y.tail_done, 0));
+  if (own && ok(hipEventRecord(y.tail_done, ts)) && join) ok(hipStreamWaitEvent(s, y.tail_done, 0));
   if (join) mark(4, s);
   return e;
 }
