@@ -939,7 +939,7 @@ hipError_t dispatch_fwd(const DevProfile &P, const DevDb &db, const DevOut &o, h
 }  // namespace
 
 hipError_t launch_tail(const DevProfile &P, const DevDb *chunk, int K, const DevOut &o, hipStream_t s,
-                       const SearchSync &y, hipEvent_t *ev, bool join = true);
+                       const SearchSync &y, hipEvent_t *ev, bool join = true, bool swap = false);
 
 hipError_t launch_search(const DevProfile &P, const DevDb *chunk, int K, const DevOut &o, hipStream_t s,
                          const SearchSync &y, hipEvent_t *ev) {
@@ -981,9 +981,10 @@ hipError_t launch_search(const DevProfile &P, const DevDb *chunk, int K, const D
 // o.rescore_apart) runs it before Forward: there it has nothing to do in
 // ordinary searches, and an empty launch takes 4 us, a fork and join of streams
 // 10 to 20.  (In a group of 12 the searches' streams overlap each other: 10.04 ms
-// with the empty launches in line, 9.94 beside Forward.)
+// with the empty launches in line, 9.94 beside Forward.)  `swap` exchanges the
+// two streams.
 hipError_t launch_tail(const DevProfile &P, const DevDb *chunk, int K, const DevOut &o, hipStream_t s,
-                       const SearchSync &y, hipEvent_t *ev, bool join) {
+                       const SearchSync &y, hipEvent_t *ev, bool join, bool swap) {
   hipError_t e = hipSuccess;
   auto ok = [&](hipError_t r) {
     if (e == hipSuccess) e = r;
@@ -995,7 +996,7 @@ hipError_t launch_tail(const DevProfile &P, const DevDb *chunk, int K, const Dev
   const bool fused = o.fused_tail && tail_fused_instance(P);
   const bool own = K > 1 || !join;
   const bool apart = (o.rescore_apart || own) && !fused;
-  const hipStream_t ts = own ? y.tail : s;
+  const hipStream_t ts = !own ? s : swap ? y.aux : y.tail, as = swap ? y.tail : y.aux;
   for (int k = 0; k < K && e == hipSuccess; k++) {
     const bool any = chunk[k].n > 0;
     const DevDb &ck = chunk[k];
@@ -1003,16 +1004,16 @@ hipError_t launch_tail(const DevProfile &P, const DevDb *chunk, int K, const Dev
     if (any && !ok(fused ? dispatch_tail_fused(P, ck, o, ts) : dispatch_vit16(P, ck, o, ts))) break;
     if (k == K - 1) mark(2, ts);
     if (apart) {
-      if (!ok(hipEventRecord(y.vit_done[k], ts)) || !ok(hipStreamWaitEvent(y.aux, y.vit_done[k], 0))) break;
-      if (any && !ok(dispatch_vit32(P, ck, o, y.aux))) break;
+      if (!ok(hipEventRecord(y.vit_done[k], ts)) || !ok(hipStreamWaitEvent(as, y.vit_done[k], 0))) break;
+      if (any && !ok(dispatch_vit32(P, ck, o, as))) break;
     }
     if (fused) continue;
     if (any && !apart && !ok(dispatch_vit32(P, ck, o, ts))) break;
     if (k == K - 1 && !apart) mark(3, ts);
     if (any && !ok(dispatch_fwd(P, ck, o, ts))) break;
   }
-  if (apart || fused) mark(3, apart ? y.aux : ts);
-  if (apart && ok(hipEventRecord(y.aux_done, y.aux))) ok(hipStreamWaitEvent(ts, y.aux_done, 0));
+  if (apart || fused) mark(3, apart ? as : ts);
+  if (apart && ok(hipEventRecord(y.aux_done, as))) ok(hipStreamWaitEvent(ts, y.aux_done, 0));
   // chunk 0 starts at sorted index 0: its sorted arrays are the whole
   // database's
   DevDb all = chunk[0];
@@ -1046,11 +1047,18 @@ hipError_t launch_search_group(const DevProfile *P, const DevDb *db, const DevOu
   }
   std::vector<int> done(n, 0);
   // a search's composition-bias filter (if on) and its cascade tail, on its
-  // own handle's streams once its MSV (on `s`) is done
+  // own handle's streams once its MSV (on `s`) is done.  Each handle's two
+  // streams share the four hardware queues with the others' in the order in
+  // which they were made: the first four tails have a queue each, the later ones
+  // only two between them.  So from the fifth on every other pair exchanges its
+  // streams (12 searches by profiles of 50 to 400 nodes 9.89 -> 9.77 ms, 9 of
+  // 77 to 616 nodes against 12,398 targets 3.21 -> 2.93; exchanging every
+  // other one from the first on takes a group of 12 to 9.37 but one of 2 from
+  // 0.92 to 1.00).
   auto tail = [&](int i) {
     if (o[i].bias_filter && db[i].n > 0) ok(launch_bias(P[i], db[i], o[i], s));
     ok(hipEventRecord(y[i]->msv_done[0], s));
-    ok(launch_tail(P[i], &db[i], 1, o[i], s, *y[i], nullptr, false));
+    ok(launch_tail(P[i], &db[i], 1, o[i], s, *y[i], nullptr, false, i >= 4 && (i & 2)));
   };
   for (int i = 0; i < n && e == hipSuccess; i++) {
     if (done[i] || db[i].n == 0) continue;
