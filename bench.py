@@ -27,9 +27,9 @@ between HIP events that the library records there, so the live launch
 duration is the stage's time divided by the launches.  Beside it,
 `algorithmic_frac` counts the nominal 4 element-ops per cell (max,
 saturating add, saturating subtract, running max) over the same time; the
-fp16 rewrite needs fewer instructions than that (one packed add and one
-packed 3-way maximum per two cells, plus its running maximum), so that
-figure can pass 1 while the issue fraction cannot.  `traffic` is the HBM
+fp16 rewrite needs fewer instructions than that (one packed add with clamp
+per two cells, and half a packed 3-way maximum for the running maximum), so
+that figure can pass 1 while the issue fraction cannot.  `traffic` is the HBM
 bytes per MSV launch that rocprofv3's FETCH_SIZE and WRITE_SIZE counters
 measured for the same kernel source (scaled by a plain 1 GiB copy), beside
 the launch's algorithmic bytes; `valu_issue` is the same instruction count
@@ -177,7 +177,7 @@ def stage_roofline(M_list, res_total, ran_cells, st_ms, chunks=1, fused=False):
         return out
     out["viterbi"] = entry(VIT_OPS_PER_CELL * ran_cells["viterbi"], st_ms[1], round(PEAK_PK16_TOPS, 2),
                            "Tops/s packed 16-bit, 18 ops/cell, cells of the targets scored to their last row "
-                           "(int16 overflows, which stop early, left out: a lower bound)")
+                           "(int16 overflows that stop early, above 768 nodes, left out: a lower bound)")
     out["rescore"] = entry(RESCORE_OPS_PER_CELL * ran_cells["rescore"], st_ms[2], round(PEAK_I32_TOPS, 2),
                            "Tops/s 32-bit, 17 ops/cell")
     # Forward runs beside the rescore; its figure here uses the time both take
@@ -351,10 +351,14 @@ def main():
         fl = out["flags"].cpu().numpy()
         vit_ran = (fl & hg.HMM_VIT_RAN) != 0
         vit_ovf = (fl & hg.HMM_VIT_OVF) != 0
+        # up to 768 nodes the int16 kernel re-bases an overflow's values and
+        # scores it to the last row: nothing is left to the rescore
+        if p.M <= 768:
+            vit_ovf &= False
         ran["viterbi"] += p.M * int(lengths[vit_ran & ~vit_ovf].sum())
         ran["viterbi_overflow"] += p.M * int(lengths[vit_ran & vit_ovf].sum())
         ran["msv_overflow"] += p.M * int(lengths[(fl & hg.HMM_MSV_OVF) != 0].sum())
-        ran["rescore"] += p.M * int(lengths[(fl & hg.HMM_VIT_OVF) != 0].sum())
+        ran["rescore"] += p.M * int(lengths[vit_ovf].sum())
         ran["forward"] += p.M * int(lengths[(fl & hg.HMM_FWD_RAN) != 0].sum())
     counts = counts.tolist()
     # stage times summed over the profiles of one step
