@@ -609,11 +609,12 @@ int hmm_profile_upload(const hmm_profile_desc *d, hmm_stream stream, hmm_profile
   // would take 2.7 us a row (M = 2,500 x 300,000 targets with 0.2 % homologs:
   // Viterbi 4.0 ms, then Forward 3.2 beside the rescore 5.4, against 7.0 and 3.2
   // re-based; 15.8 against 16.4 ms a search).
-  int msc_min = 0, mi_min = 0;
+  int msc_min = 0, mi_min = 0, isc_max = 0;
   for (int16_t v : p->msc16) msc_min = std::min(msc_min, (int)v);
+  for (int16_t v : p->isc16) isc_max = std::max(isc_max, (int)v);
   for (int k = 1; k < M; k++) mi_min = std::min(mi_min, t16(k, 1));
   dv.s_max = p->s_max;
-  dv.rebase_w = p->s_max <= 12000 && !coop_instance(Q32) ? -msc_min - mi_min : 1 << 20;
+  dv.rebase_w = p->s_max <= 12000 && !coop_instance(Q32) ? isc_max - msc_min - mi_min : 1 << 20;
   dv.entry_p = (float)(2.0 / ((double)M * ((double)M + 1.0)));
   for (int a = 0; a < kAlpha; a++) {
     double m = 0.0;

@@ -160,14 +160,16 @@ __global__ void reset_ovf(int32_t *c) {
 // then the exact int32 score, and the overflow flag says that some true value
 // reached 32767.  Values that fall below the stored floor F = -32768 are clipped
 // there, which changes nothing while
-//   xBe - off >= F + W,  W = - min msc - min MI     (*)
-// since then no match value (at least xBe + msc) is clipped, a clipped insert
-// value lies below M + MI, the insert maximum's other term, and below xBe where
-// it enters a match maximum, and the delete floor lies above F.  xBe never
-// decreases, so (*) is tested with the first row's (where it fails the target is
-// not re-based) and, with the xBe that the latest row used, at every re-basing
-// (where it fails the target goes to the int32 rescore, as every overflow of a
-// target that is not re-based does).
+//   xBe - off >= F + W,  W = max(0, max isc) - min msc - min MI     (*)
+// No match value is clipped: it is at least xBe + msc.  An insert value above
+// its true one is at most F + max isc: the first row's is F + isc, from cells
+// that start at F, and a later one is F itself, a clipped true value.  A row
+// later it lies at or below M + MI, the insert maximum's other term, and at or
+// below xBe where it enters a match maximum, so nothing more comes of it.  The
+// delete floor lies above F.  xBe never decreases, so (*) is tested with the
+// first row's (where it fails the target is not re-based) and, with the xBe that
+// the latest row used, at every re-basing (where it fails the target goes to the
+// int32 rescore, as every overflow of a target that is not re-based does).
 //
 // Measured with every overflow left to the rescore, and re-based: M = 734 x 1M
 // targets (1 % homologs), Viterbi 2.50 and 2.74 ms and the rescore 1.68 ms and

@@ -8,6 +8,7 @@ import pytest
 
 import oracle
 import paper_2111_06340_amd as hg
+import test_viterbi_rebase_model as model
 from synth import gen
 
 pytestmark = pytest.mark.gpu
@@ -86,3 +87,37 @@ def test_overflows(M, kind):
                 bad = np.nonzero(g[k] != o[k])[0]
                 assert bad.size == 0, f"M={M} {kind}: {k} differs at {bad[:5]}: {g[k][bad[:5]]} {o[k][bad[:5]]}"
             assert g["counts"][1] == n_ovf
+
+
+def _compare(prof, seqs, what):
+    """Scores, flags and the overflow count of both ways to run the stages; returns the overflows."""
+    import torch
+    off = np.zeros(len(seqs) + 1, np.int64)
+    off[1:] = np.cumsum([s.size for s in seqs])
+    res = np.concatenate(seqs)
+    o = oracle.search(oracle.OracleProfile(prof), res, off, (0.0, 0.0, 0.0), F, nthreads=8)
+    n_ovf = int(np.sum((o["flags"] & oracle.F_VIT_OVF) != 0))
+    P, D = hg.Profile(prof, 0.0, 0.0, 0.0), hg.Database(res, off)
+    for mode in (1, 2):
+        print(f"[rebase] {what} M={prof.M} mode={mode} n={D.n} overflows={n_ovf}", flush=True)
+        hg.hmm_db_fused_tail(D.handle, mode)
+        out = hg.search(P, D, F)
+        torch.cuda.synchronize()
+        g = {k: v.cpu().numpy() for k, v in out.items()}
+        for k in ("vit", "flags"):
+            bad = np.nonzero(g[k] != o[k])[0]
+            assert bad.size == 0, f"{what} M={prof.M}: {k} differs at {bad[:5]}: {g[k][bad[:5]]} {o[k][bad[:5]]}"
+        assert g["counts"][1] == n_ovf
+    return n_ovf
+
+
+@pytest.mark.parametrize("M,ins,ii", model.SWEEP)
+def test_insert_before_the_first_match(M, ins, ii):
+    for mi in model.MI:
+        prof, c = model.peaked(M, 0.7, ins, mi, ii)
+        assert _compare(prof, model.insert_first(prof, c), f"M->I {mi:.1e}") > 0
+
+
+def test_insert_at_a_lone_node():
+    for prof, seqs in model.lone_node():
+        _compare(prof, seqs, "lone node")
