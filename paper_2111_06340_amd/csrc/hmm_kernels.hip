@@ -168,8 +168,10 @@ __global__ void reset_ovf(int32_t *c) {
 // below xBe where it enters a match maximum, so nothing more comes of it.  The
 // delete floor lies above F.  xBe never decreases, so (*) is tested with the
 // first row's (where it fails the target is not re-based) and, with the xBe that
-// the latest row used, at every re-basing (where it fails the target goes to the
-// int32 rescore, as every overflow of a target that is not re-based does).
+// the latest row used, at every re-basing.  Where it fails at the first one, no
+// value has reached 32767 yet: the target goes on without re-basing, and to the
+// int32 rescore if one does.  Where it fails later, one has (two re-basings are
+// at least RL + 1 + (RL + 1 - kRebaseTo) > 32767 up), and it goes there at once.
 //
 // Measured with every overflow left to the rescore, and re-based: M = 734 x 1M
 // targets (1 % homologs), Viterbi 2.50 and 2.74 ms and the rescore 1.68 ms and
@@ -220,9 +222,8 @@ __device__ __forceinline__ VitResult vit16_target(const uint32_t *__restrict__ e
   uint32_t xbe2 = splat16(sat16(xbt));
   auto floor_of = [&](int xbe) { return splat16(min(xbe - P.dm_max16, 32767)); };
   uint32_t tau2 = floor_of(sat16(mv + entry));
-  const bool reb = kRebase16<Q> && mv + entry >= kNeg16 + P.rebase_w;
-  const int RL = reb ? 32766 - P.s_max : 32766;
-  const uint32_t rl2 = splat16(RL);
+  bool reb = kRebase16<Q> && mv + entry >= kNeg16 + P.rebase_w;
+  int RL = reb ? 32766 - P.s_max : 32766;
   int off = 0, top = 0;   // top: the largest true value at a re-basing
   // trigger: some accM > tm1, or some accI > RL, i.e. accI + iadj > tm1
   uint32_t tm1 = splat16(min(-ej, 32766));
@@ -300,7 +301,7 @@ __device__ __forceinline__ VitResult vit16_target(const uint32_t *__restrict__ e
     const uint32_t acc = kRebase16<Q> ? i16_max(accM, i16_adds(accI, iadj)) : accM;
     if (__builtin_expect(any_lane(i16_max(acc, tm1) != tm1), 0)) {
       const int m = wave_max_i32(hmax16(accM));
-      if (m > RL || (kRebase16<Q> && any_lane(i16_max(accI, rl2) != rl2))) return true;
+      if (m > RL || (kRebase16<Q> && any_lane(i16_max(accI, splat16(RL)) != splat16(RL)))) return true;
       settle(m);
     }
     return false;
@@ -318,12 +319,20 @@ __device__ __forceinline__ VitResult vit16_target(const uint32_t *__restrict__ e
     }
     const int m = wave_max_i32(hmax16(accM));
     const int hi = max(m, wave_max_i32(hmax16(accI))), sh = hi - kRebaseTo;
+    if (xbt - off - sh < kNeg16 + P.rebase_w) {
+      if (off > 0) {
+        res.redo = true;
+        break;
+      }
+      reb = false;
+      RL = 32766;
+      iadj = kNegNeg;
+      settle(m);
+      r = stop + 1;
+      continue;
+    }
     top = max(top, hi + off);
     off += sh;
-    if (xbt - off < kNeg16 + P.rebase_w) {
-      res.redo = true;
-      break;
-    }
     const uint32_t sh2 = splat16(sh);
 #pragma unroll
     for (int q = 0; q < Q; q++) {

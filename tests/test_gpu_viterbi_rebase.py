@@ -121,3 +121,9 @@ def test_insert_before_the_first_match(M, ins, ii):
 def test_insert_at_a_lone_node():
     for prof, seqs in model.lone_node():
         _compare(prof, seqs, "lone node")
+
+
+@pytest.mark.parametrize("M", [3, 64, 128, 256, 384, 385, 768])
+def test_insert_short_of_the_limit(M):
+    prof, seqs = model.insert_to_the_limit(M)
+    assert 0 < _compare(prof, seqs, "insert to the limit") < len(seqs)

@@ -23,7 +23,7 @@ def rebase_room(t, M):
     return -msc_min - mi_min + isc_max
 
 
-def vit16_model(t, M, mv, x, W):
+def vit16_model(t, M, mv, x, W, carry_on=True):
     """(score, overflow, left to the rescore) of the re-based kernel."""
     sat = lambda v: np.clip(v, NEG, TOP)  # noqa: E731
     z = np.full((1,), NEG)
@@ -62,8 +62,11 @@ def vit16_model(t, M, mv, x, W):
             hi = max(accM, accI)
             sh = hi - REBASE_TO
             if xbt - off - sh < NEG + W:
-                redo = True
-                break
+                if carry_on and off == 0:   # nothing has passed the range yet: go on without re-basing
+                    reb, RL = False, TOP - 1
+                else:
+                    redo = True
+                    break
             else:
                 top = max(top, hi + off)
                 off += sh
@@ -81,15 +84,15 @@ def vit16_model(t, M, mv, x, W):
     return (m + ej + mv if ovf else int(sat(sat(m + ej) + mv))), ovf, False
 
 
-def agrees(prof, seqs, W=rebase_room):
+def agrees(prof, seqs, **mutant):
     """Targets on which the model and the oracle differ, and how the targets were scored."""
     t = hg.hmm_debug_tables(prof)
     op = oracle.OracleProfile(prof)
-    W = W(t, prof.M)
+    W = mutant.pop("W", rebase_room)(t, prof.M)
     bad, n = [], dict(rebased=0, overflow=0, redo=0)
     for j, x in enumerate(seqs):
         mv = oracle.length_params(len(x))["move16"]
-        raw, ovf, redo = vit16_model(t, prof.M, mv, x, W)
+        raw, ovf, redo = vit16_model(t, prof.M, mv, x, W, **mutant)
         want, o = oracle.vit16(op, x)
         if o:
             want = oracle.vit32(op, x)
@@ -138,6 +141,13 @@ def lone_node():
     return out
 
 
+def insert_to_the_limit(M):
+    """An insert that is all but never left: its value alone nears the limit while xBe stays low."""
+    prof, c = peaked(M, 0.9, 0.8, 0.05, 0.5)
+    prof.trans[:, 3:5] = [1e-15, 1.0 - 1e-15]
+    return prof, [np.concatenate([c[: k], np.zeros(n, np.uint8)]) for k in (1, 2) for n in range(8, 61)]
+
+
 MI = [1e-3, 1e-5, 10 ** -8.7, 1e-12, 1e-14, 1e-16, 1e-17, 1e-19]
 SWEEP = [(M, ins, ii) for M in (3, 20, 128) for ins, ii in ((0.3, 0.9), (0.8, 0.95))]
 
@@ -156,9 +166,43 @@ def test_insert_at_a_lone_node():
         assert not bad, (prof.M, bad, n)
 
 
-def test_the_sweeps_reach_the_rules_edge():
-    """Without the insert score in W, the model and the oracle disagree on these inputs."""
+@pytest.mark.parametrize("M", [3, 64, 128, 256])
+def test_insert_short_of_the_limit(M):
+    prof, seqs = insert_to_the_limit(M)
+    bad, n = agrees(prof, seqs)
+    assert not bad, (bad, n)
+    assert 0 < n["overflow"] < len(seqs)
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_random_profiles(seed):
+    rng = np.random.default_rng(seed)
+    hits = 0
+    for _ in range(40):
+        M = int(rng.integers(1, 13))
+        prof, c = peaked(M, 1 - 10 ** rng.uniform(-3, -0.3), rng.uniform(0.05, 0.99), 10 ** rng.uniform(-14, -1.5),
+                         rng.uniform(0.05, 0.999))
+        rnd = lambda *s: np.maximum(rng.dirichlet(np.full(20, 10 ** rng.uniform(-1.5, 0)), size=s), 1e-9)  # noqa: E731
+        if rng.random() < 0.5:
+            prof.match[:] = rnd(M)
+            prof.match /= prof.match.sum(1, keepdims=True)
+            if M > 1:
+                prof.insert[:] = rnd(M - 1)
+                prof.insert /= prof.insert.sum(1, keepdims=True)
+        seqs = insert_first(prof, c) + [rng.integers(0, 20, size=int(rng.integers(1, 200))).astype(np.uint8)
+                                        for _ in range(4)]
+        bad, n = agrees(prof, seqs)
+        assert not bad, (M, bad, n)
+        hits += n["rebased"]
+    assert hits > 20
+
+
+def test_the_sweeps_reach_the_rules_edges():
+    """Without the insert score in W, or with a value that only nears the limit
+    taken for an overflow, the model and the oracle disagree on these inputs."""
     def narrow(t, M):
         return rebase_room(t, M) - max([0] + [int(v) for v in t["isc16"].reshape(-1)])
     prof, c = peaked(3, 0.7, 0.8, 1e-16, 0.95)
     assert any(agrees(p, s, W=narrow)[0] for p, s in lone_node() + [(prof, insert_first(prof, c))])
+    prof, seqs = insert_to_the_limit(128)
+    assert agrees(prof, seqs, carry_on=False)[0]
