@@ -222,7 +222,7 @@ __device__ __forceinline__ VitResult vit16_target(const uint32_t *__restrict__ e
   uint32_t xbe2 = splat16(sat16(xbt));
   auto floor_of = [&](int xbe) { return splat16(min(xbe - P.dm_max16, 32767)); };
   uint32_t tau2 = floor_of(sat16(mv + entry));
-  bool reb = kRebase16<Q> && mv + entry >= kNeg16 + P.rebase_w;
+  const bool reb = kRebase16<Q> && mv + entry >= kNeg16 + P.rebase_w;
   int RL = reb ? 32766 - P.s_max : 32766;
   int off = 0, top = 0;   // top: the largest true value at a re-basing
   // trigger: some accM > tm1, or some accI > RL, i.e. accI + iadj > tm1
@@ -313,23 +313,20 @@ __device__ __forceinline__ VitResult vit16_target(const uint32_t *__restrict__ e
     int stop = 0;
     if (!drive_rows(x, L, r, 0, stop, lane, ea, eb, load, row)) break;
     // a value above RL (32766 without re-basing: an overflow)
-    if (!reb) {
+    if (!reb || RL == 32766) {
       res.redo = true;
       break;
     }
     const int m = wave_max_i32(hmax16(accM));
-    const int hi = max(m, wave_max_i32(hmax16(accI))), sh = hi - kRebaseTo;
+    const int hi = max(m, wave_max_i32(hmax16(accI)));
+    int sh = hi - kRebaseTo;
     if (xbt - off - sh < kNeg16 + P.rebase_w) {
       if (off > 0) {
         res.redo = true;
         break;
       }
-      reb = false;
-      RL = 32766;
-      iadj = kNegNeg;
-      settle(m);
-      r = stop + 1;
-      continue;
+      RL = 32766;   // no value has reached 32767: on without re-basing
+      sh = 0;
     }
     top = max(top, hi + off);
     off += sh;
