@@ -2,8 +2,10 @@
 of vectors per lane or waves per target, with random transitions at every node
 (a value taken from the wrong neighbour at a lane's, or a wave's, edge changes
 the posteriors) and with zero-probability transitions (the gated instances)."""
+import numpy as np
 import pytest
 
+import paper_2111_06340_amd as hg
 from conftest import random_profile
 from synth import gen
 from test_gpu_decode import _check_selection, compare_decode, gpu, run  # noqa: F401
@@ -42,3 +44,21 @@ def test_regions_at_both_ends():
     res, g = run(prof, res_, off, (0.0, 0.0, 0.0), (1.0, 1.0, 1.0), decode_all=True)
     compare_decode(prof, res_, off, g, _check_selection(res, g, True), "ends")
     assert any(d["s"] == 1 for d in g["doms"])
+
+
+@pytest.mark.parametrize("M,longest", [(256, 3900), (256, 7000), (384, 8200), (734, 5300), (734, 8000), (1500, 3000)])
+def test_few_slots(M, longest):
+    """Static scratch for 9 to 20 blocks: every target decoded once, as with as many slots as fit the chip."""
+    import torch
+    prof = gen.make_profile(M, 8000 + M)
+    rng = np.random.default_rng(M)
+    lengths = [longest] + [int(v) for v in rng.integers(20, 90, size=300)]
+    res_, off = _ragged_db(prof, M, lengths=lengths, homolog_every=3)
+    P, D = hg.Profile(prof, 0.0, 0.0, 0.0), hg.Database(res_, off)
+    announce(f"few slots M={M} longest={longest} n={D.n}")
+    a, b = (hg.decode(P, D, None, pp=True, aln=True, static=s) for s in (True, False))
+    torch.cuda.synchronize()
+    assert hg.domains_table(a) == hg.domains_table(b)
+    for k in ("n_dom", "exp_dom", "pp", "aln"):
+        assert torch.equal(a[k], b[k]), k
+    assert bool(torch.isfinite(a["exp_dom"]).all())
