@@ -459,6 +459,8 @@ int hmm_profile_upload(const hmm_profile_desc *d, hmm_stream stream, hmm_profile
   {
     const int n = 64 * Qd, nw = 64 * dqw;   // cells, cells per wave
     auto dd = [&](int c) { return c < n ? tr_prob(TR_DDIN, c) : 0.0; };   // into delete cell c
+    // whether the alignment may take that transition: the kernel's floats decide
+    auto dd_open = [&](int c) { return (float)dd(c) > 0.0f; };
     auto at = [&](int k, int c) -> float & {
       const int l = c / dqw;
       return h_dtr[((size_t)k * Qd + (l / 64) * dqw + c % dqw) * kWave + l % 64];
@@ -490,12 +492,12 @@ int hmm_profile_upload(const hmm_profile_desc *d, hmm_stream stream, hmm_profile
       }
       // from the next lane's first delete cell (none past the wave) back to this one
       acc = l % 64 < 63 ? dd((l + 1) * dqw) : 1.0;
-      bool open = acc > 0.0;
+      bool open = l % 64 == 63 || dd_open((l + 1) * dqw);
       for (int c = (l + 1) * dqw - 1; c >= l * dqw; c--) {
         at(DT_SUF, c) = (float)acc;
         at(DT_GSUF, c) = open ? 0.0f : -INFINITY;
         acc *= dd(c);
-        open = open && dd(c) > 0.0;
+        open = open && dd_open(c);
       }
     }
     std::vector<double> fl(dw), pj(dw), bf(dw), bj(dw);   // per wave: factors through its delete cells and out of them
@@ -516,14 +518,14 @@ int hmm_profile_upload(const hmm_profile_desc *d, hmm_stream stream, hmm_profile
         if (c > a) at(DT_BMD, c - 1) = (float)(tr_prob(TR_MDIN, c) * acc);
         if (c > a) {
           acc *= dd(c);
-          open = open && dd(c) > 0.0;
+          open = open && dd_open(c);
         }
       }
       at(DT_BMD, b - 1) = 0.0f;   // the next wave's cell: added on its own
       bf[w] = acc;
       bj[w] = acc * dd(a);
       gf[w] = open;
-      gj[w] = open && dd(a) > 0.0;
+      gj[w] = open && dd_open(a);
       float *edge = h_dconst + kDecEdge + w * 4;
       edge[0] = (float)(b < n ? tr_prob(TR_MDIN, b) : 0.0);
       edge[1] = (float)dd(b);

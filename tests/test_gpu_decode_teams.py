@@ -62,3 +62,27 @@ def test_few_slots(M, longest):
     for k in ("n_dom", "exp_dom", "pp", "aln"):
         assert torch.equal(a[k], b[k]), k
     assert bool(torch.isfinite(a["exp_dom"]).all())
+
+
+@pytest.mark.parametrize("M", [60, 150, 600, 1100])
+def test_transitions_below_the_float_range(M):
+    """A transition that is 0 in the kernel's floats is closed like a 0, also across lanes and waves."""
+    import torch
+    prof = gen.make_profile(M, 8100 + M)
+    rng = np.random.default_rng(M)
+    seqs = []
+    for gap in (3, 20, M // 3):   # homologs without a stretch of nodes: the alignment would delete them
+        h = prof.match.argmax(axis=1).astype(np.uint8)
+        at = int(rng.integers(5, M - gap - 5))
+        seqs.append(np.concatenate([h[:at], h[at + gap:]]))
+    off = np.concatenate([[0], np.cumsum([s.size for s in seqs])]).astype(np.int64)
+    D = hg.Database(np.concatenate(seqs), off)
+    announce(f"transitions below the float range M={M} n={D.n}")
+    got = []
+    for dd in (0.0, 1e-50):
+        prof.trans[:, 5:7] = [1.0 - dd, dd]
+        got.append(hg.decode(hg.Profile(prof, 0.0, 0.0, 0.0), D, None, pp=True, aln=True))
+        torch.cuda.synchronize()
+    assert hg.domains_table(got[0]) == hg.domains_table(got[1])
+    for k in ("exp_dom", "pp", "aln"):
+        assert torch.equal(got[0][k], got[1][k]), k
