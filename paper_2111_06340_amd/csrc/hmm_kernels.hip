@@ -1059,10 +1059,13 @@ hipError_t launch_search_group(const DevProfile *P, const DevDb *db, const DevOu
   // streams share the four hardware queues with the others' in the order in
   // which they were made: the first four tails have a queue each, the later ones
   // only two between them.  So from the fifth on every other pair exchanges its
-  // streams (12 searches by profiles of 50 to 400 nodes 9.89 -> 9.77 ms, 9 of
-  // 77 to 616 nodes against 12,398 targets 3.21 -> 2.93; exchanging every
-  // other one from the first on takes a group of 12 to 9.37 but one of 2 from
-  // 0.92 to 1.00).
+  // streams.  What that gives depends on the streams that the process made
+  // before.  Without and with the exchange, handles made one after another: 8
+  // searches by profiles of 50 to 330 nodes 4.02 and 3.79 ms, 9 of 77 to 616 3.15
+  // and 3.08, 12 of 50 to 400 9.99 and 9.83, 16 of 50 to 500 10.82 and 10.29; with
+  // one to three other streams made and used before, between 6 % faster and 2 %
+  // slower.  Exchanging every other one from the first on: 12 in 9.45, 16 in 9.9,
+  // but 2 in 0.94 or 1.30, depending on those streams.
   auto tail = [&](int i) {
     if (o[i].bias_filter && db[i].n > 0) ok(launch_bias(P[i], db[i], o[i], s));
     ok(hipEventRecord(y[i]->msv_done[0], s));
