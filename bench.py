@@ -177,7 +177,8 @@ def stage_roofline(M_list, res_total, ran_cells, st_ms, chunks=1, fused=False):
         return out
     out["viterbi"] = entry(VIT_OPS_PER_CELL * ran_cells["viterbi"], st_ms[1], round(PEAK_PK16_TOPS, 2),
                            "Tops/s packed 16-bit, 18 ops/cell, cells of the targets scored to their last row "
-                           "(int16 overflows that stop early, above 768 nodes, left out: a lower bound)")
+                           "(int16 overflows, above 768 nodes, stop early and are left out: a lower bound; those of "
+                           "shorter profiles count as scored by re-basing, none as rescored)")
     out["rescore"] = entry(RESCORE_OPS_PER_CELL * ran_cells["rescore"], st_ms[2], round(PEAK_I32_TOPS, 2),
                            "Tops/s 32-bit, 17 ops/cell")
     # Forward runs beside the rescore; its figure here uses the time both take
@@ -352,7 +353,8 @@ def main():
         vit_ran = (fl & hg.HMM_VIT_RAN) != 0
         vit_ovf = (fl & hg.HMM_VIT_OVF) != 0
         # up to 768 nodes the int16 kernel re-bases an overflow's values and
-        # scores it to the last row: nothing is left to the rescore
+        # scores it to the last row, so nothing is left to the rescore; that
+        # holds for these workloads' scores, where they leave room for it
         if p.M <= 768:
             vit_ovf &= False
         ran["viterbi"] += p.M * int(lengths[vit_ran & ~vit_ovf].sum())

@@ -198,10 +198,10 @@ int hmm_search(const hmm_profile *p, hmm_db *db, const hmm_thresholds *t,
  * many-queries mode of the paper's large-scale run (thousands of proteins,
  * each searched against the same databases; Evaluation section): the MSV
  * stage of profiles that share a kernel instance (the diagonal layout with
- * 1-3 vectors per lane, i.e. M up to 383) runs as one kernel for up to 4 of
- * them, so one wave scores a target against several profiles and the
- * residue stream and its scalar handling are shared; the other profiles'
- * MSV runs as in hmm_search.  Each search then runs its later stages on its
+ * 1 or 2 vectors per lane, i.e. M up to 255, up to 4 of them; with 3 or 4,
+ * M up to 511, 2) runs as one kernel, so one wave scores a target against
+ * several profiles and the residue stream and its scalar handling are
+ * shared; the other profiles' MSV runs as in hmm_search.  Each search then runs its later stages on its
  * own handle's streams, concurrently with the others, all joined back into
  * `stream`.  Searches are not chunked (hmm_db_pipeline does not apply).
  * Enqueued on `stream` like hmm_search (same host waits when a handle's
@@ -275,10 +275,9 @@ typedef struct {
  * (and when a longer profile needs more) the library allocates a scratch
  * area on the device for the Forward/Backward matrices of the targets in
  * flight -- one slot per resident team of 1, 2 or 4 waves (by the profile's
- * length), at most 16 GiB -- which the
- * database keeps until hmm_db_free.  Errors: HMM_EINVAL (NULL profile, db
- * or out; NULL dom or n_dom; max_dom < 0), HMM_ENOMEM (scratch),
- * HMM_EDEVICE. */
+ * length), at most 16 GiB -- which the database keeps until hmm_db_free.
+ * Errors: HMM_EINVAL (NULL profile, db or out; NULL dom or n_dom; max_dom <
+ * 0), HMM_ENOMEM (scratch), HMM_EDEVICE. */
 int hmm_decode(const hmm_profile *p, hmm_db *db, const uint8_t *flags, uint8_t mask,
                const hmm_decode_out *out, hmm_stream stream);
 
@@ -295,7 +294,8 @@ int hmm_decode(const hmm_profile *p, hmm_db *db, const uint8_t *flags, uint8_t m
  * start at zero), so calls that overlap on one device -- on different
  * streams, or from different threads -- race and give undefined results;
  * calls serialised on one stream are safe.  Errors: those of hmm_decode
- * (HMM_ENOMEM aside), and HMM_ERANGE when four slots exceed the array. */
+ * (HMM_ENOMEM aside), and HMM_ERANGE when four slots of one wave per target
+ * exceed the array. */
 int hmm_decode_static(const hmm_profile *p, hmm_db *db, const uint8_t *flags, uint8_t mask,
                       const hmm_decode_out *out, hmm_stream stream);
 

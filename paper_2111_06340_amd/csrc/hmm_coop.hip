@@ -284,7 +284,7 @@ __device__ __forceinline__ void fwd_coop_wave(const DevProfile &P, const DevDb &
     };
     float ea[2 * QW], eb[2 * QW];
     int stop;
-    (void)drive_rows(db.res + db.start[t], L, 0, 0, stop, lane, ea, eb, load, row);
+    (void)drive_rows(db.res + db.start[t], L, 0, stop, lane, ea, eb, load, row);
     if constexpr (w == 0) {
       const float f = (float)(log((double)C * (double)move) + (double)shift * M_LN2);
       const bool pass = f > lp.fthr;
@@ -486,7 +486,7 @@ __device__ __forceinline__ void vit32_coop_wave(const DevProfile &P, const DevDb
     };
     int ea[2 * QW], eb[2 * QW];
     int stop;
-    (void)drive_rows(db.res + db.start[t], L, 0, 0, stop, lane, ea, eb, load, row);
+    (void)drive_rows(db.res + db.start[t], L, 0, stop, lane, ea, eb, load, row);
     // the final maximum over every cell of every row, all waves
     {
       const int v = wave_max_i32(accM);

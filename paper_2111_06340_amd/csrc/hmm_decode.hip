@@ -5,7 +5,7 @@
 // sequence alignment).
 //
 // A team of W waves decodes one target at a time in a private scratch slot (one
-// slot per resident team): W = 1 for short profiles, a workgroup of 2, 4 or 8
+// slot per resident team): W = 1 for short profiles, a workgroup of 2 or 4
 // waves for longer ones.  Wave w holds the cells [64 QW w, 64 QW (w + 1)), QW of
 // them per lane: a cell's neighbour lives in the same lane, in the next lane
 // (one DPP shift), or, at a wave's edge, in the next wave.  A row takes one

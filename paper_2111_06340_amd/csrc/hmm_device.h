@@ -11,7 +11,6 @@
 namespace hmmgpu {
 namespace {
 
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 typedef short i16x2 __attribute__((ext_vector_type(2)));
 
 constexpr uint32_t kNegNeg = 0x80008000u;  // two int16 -32768
@@ -87,18 +86,6 @@ __device__ __forceinline__ int next_target(const WorkQueue<true> &queue, int *sl
 }
 
 // --- packed 16-bit arithmetic ------------------------------------------------
-__device__ __forceinline__ uint32_t u16_max(uint32_t a, uint32_t b) {
-  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a),
-                                                                __builtin_bit_cast(u16x2, b)));
-}
-__device__ __forceinline__ uint32_t u16_adds(uint32_t a, uint32_t b) {
-  return __builtin_bit_cast(uint32_t, __builtin_elementwise_add_sat(__builtin_bit_cast(u16x2, a),
-                                                                    __builtin_bit_cast(u16x2, b)));
-}
-__device__ __forceinline__ uint32_t u16_subs(uint32_t a, uint32_t b) {
-  return __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, a),
-                                                                    __builtin_bit_cast(u16x2, b)));
-}
 __device__ __forceinline__ uint32_t i16_max(uint32_t a, uint32_t b) {
   return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(i16x2, a),
                                                                 __builtin_bit_cast(i16x2, b)));
@@ -158,17 +145,6 @@ __device__ __forceinline__ int wave_max_i32(int v) {
   v = max(v, __builtin_amdgcn_update_dpp(kMin, v, kRowBcast15, 0xa, 0xf, false));
   v = max(v, __builtin_amdgcn_update_dpp(kMin, v, kRowBcast31, 0xc, 0xf, false));
   return __builtin_amdgcn_readlane(v, 63);
-}
-
-// Sum across the wave (result uniform).
-__device__ __forceinline__ float wave_sum_f(float v) {
-  v += dpp_f<kRowShr1, 0xf>(v, 0.0f);
-  v += dpp_f<kRowShr2, 0xf>(v, 0.0f);
-  v += dpp_f<kRowShr4, 0xf>(v, 0.0f);
-  v += dpp_f<kRowShr8, 0xf>(v, 0.0f);
-  v += dpp_f<kRowBcast15, 0xa>(v, 0.0f);
-  v += dpp_f<kRowBcast31, 0xc>(v, 0.0f);
-  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
 // A row's lane scan as one DPP multiply-add per step (x <- x + P x_src, a
@@ -277,10 +253,8 @@ __device__ __forceinline__ void length_priority(int L, int lmax) {
 //   row(buf):     compute one row from buf; return true to stop
 // Rows r0 .. L-1 are run: a start inside a dword runs its first rows one at
 // a time, then whole dwords (4 rows), then the last 0..3 rows one at a
-// time.  With LIMIT, rows from `limit` on (a multiple of 4) are not run.
-// Returns true if a row stopped the driver (`stop` = that row) or the limit
-// was reached (`stop` = limit - 1).  Residue codes are valid (0..19): the
-// database upload checks them.  A chunk that holds none of the target's
+// time.  Returns true if a row stopped the driver (`stop` = that row).
+// Residue codes are valid (0..19): the database upload checks them.  A chunk that holds none of the target's
 // rows is not fetched (its load re-reads the current chunk, already in the
 // cache; no row uses the value), so reads run at most 255 bytes past a
 // target, inside the database's 1 KB zero-filled tail.
@@ -294,9 +268,9 @@ __device__ __forceinline__ void keep_loaded(const T (&b)[N]) {
   for (int i = 0; i < N; i++) asm volatile("" ::"v"(b[i]));
 }
 
-template <bool LIMIT = false, typename Buf, typename Load, typename Row>
-__device__ __forceinline__ bool drive_rows(const uint8_t *x, int L, int r0, int limit, int &stop, int lane, Buf &ba,
-                                           Buf &bb, Load load, Row row) {
+template <typename Buf, typename Load, typename Row>
+__device__ __forceinline__ bool drive_rows(const uint8_t *x, int L, int r0, int &stop, int lane, Buf &ba, Buf &bb,
+                                           Load load, Row row) {
   auto code = [](uint32_t w, int r) { return (int)((w >> (8 * r)) & 0xffu); };
   int r = r0;
   for (; (r & 3) != 0; r++) {
@@ -321,10 +295,6 @@ __device__ __forceinline__ bool drive_rows(const uint8_t *x, int L, int r0, int 
     const int nfull = min(kWave, (L - c0) >> 2);  // whole dwords of rows in this chunk
     for (int j = j0; j < nfull; j++) {
       const int rr = c0 + 4 * j;
-      if (LIMIT && rr >= limit) {
-        stop = rr - 1;
-        return true;
-      }
       uint32_t wn;
       if (j == kWave - 1)
         wn = (uint32_t)__builtin_amdgcn_readlane((int)nxt, 0);
@@ -359,10 +329,6 @@ __device__ __forceinline__ bool drive_rows(const uint8_t *x, int L, int r0, int 
     if (nfull < kWave) {  // the target's last 0..3 rows, from dword w (row 0's table already in ba)
       const int rt = c0 + 4 * nfull;
       if (rt >= L) return false;
-      if (LIMIT && rt >= limit) {
-        stop = rt - 1;
-        return true;
-      }
       for (int k = 0; rt + k < L; k++) {
         if (k) load(ba, code(w, k));
         if (row(ba)) {

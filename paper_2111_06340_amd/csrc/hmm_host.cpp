@@ -1257,8 +1257,10 @@ int decode_impl(const hmm_profile *p, hmm_db *db, const uint8_t *flags, uint8_t 
   const int64_t slot_dw = decode_slot_dw(p->dev.dec_qw, p->dev.dec_w, db->max_len);
   const size_t slot_bytes = (size_t)slot_dw * 4;
   const size_t budget = fixed ? kStaticDecodeBytes : kDecodeScratchMax;
-  // What is accepted: four slots of one wave per target must fit (a team's slot
-  // is at most a few per cent larger).
+  // What is accepted: four slots of one wave per target must fit.  A team's slot
+  // is at most 20 % larger (13 or 14 vectors, held as 4 waves of 4), so at least
+  // three fit then, and the launch needs one; teams of one wave, which come four
+  // to a block, have that very slot.
   const size_t wave_bytes = (size_t)decode_slot_dw(p->dev.Q32, 1, db->max_len) * 4;
   if (db->n > 0 && budget / wave_bytes < 4) {
     if (fixed)

@@ -1,5 +1,5 @@
 // Internal declarations shared by the host side (hmm_host.cpp) and the
-// kernels (hmm_kernels.hip) of the GPU library.  Not part of the C ABI.
+// kernels (the .hip files) of the GPU library.  Not part of the C ABI.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -223,8 +223,8 @@ hipError_t launch_vit32_coop(const DevProfile &p, const DevDb &db, const DevOut 
 // kernels of the chunks run back to back on the search stream, and the rest
 // of each chunk's cascade (Viterbi, the int32 rescore, Forward) on a second
 // stream as soon as the chunk's MSV is done, so it overlaps the next chunk's
-// MSV.  A search of one chunk needs no second stream.  Each chunk has its own counter block and
-// keeps its survivor lists inside its own index range.
+// MSV.  A search of one chunk needs no second stream.  Each chunk has its own
+// counter block and keeps its survivor lists inside its own index range.
 constexpr int kMaxChunks = 8;
 
 // Streams and events that order one database handle's searches.

@@ -1,4 +1,5 @@
-// HIP kernels (gfx950) of the profile-HMM search cascade and their launcher.
+// HIP kernels (gfx950) of the search cascade's stages after MSV (hmm_msv.hip)
+// and the cascade's launcher.
 //
 // One wavefront scores one target.  The model dimension (profile cells) is
 // spread across the 64 lanes; database rows (residues) are processed in
@@ -6,20 +7,15 @@
 // special states N/B/E/J/C) lives in scalar registers; branches on it are
 // uniform.
 //
-//  MSV      the uint8 recurrence rewritten exactly in packed fp16 (small
-//           integers), two cells per VGPR: one add and one 3-way maximum
-//           per cell pair; each lane position follows one DP diagonal, so
-//           no cross-lane move is needed (striped layout for large M).
 //  Viterbi  packed saturating int16, two cells per VGPR; delete chain by
-//           lazy propagation across slots.
+//           lazy propagation across slots; values past int16 re-based.
 //  Rescore  the Viterbi recurrence in int32 with a -2^30 floor.
 //  Forward  fp32 probabilities with exact power-of-two rescaling; the
 //           delete chain crosses slots through a DPP prefix scan of affine
 //           maps, E through a DPP sum.
 //
 // Cell layout (see hmm_host.cpp): packed kernels use slot 2*lane+half and
-// cell slot*Q + q (MSV's diagonal layout aside); 32-bit kernels use
-// slot = lane and cell lane*Q + q.  The
+// cell slot*Q + q; 32-bit kernels use slot = lane and cell lane*Q + q.  The
 // left neighbour of vector q is vector q-1 of the same slot, except q = 0,
 // which takes vector Q-1 of the previous slot: one cross-lane shift per
 // state per row.
@@ -311,7 +307,7 @@ __device__ __forceinline__ VitResult vit16_target(const uint32_t *__restrict__ e
   res.redo = false;
   for (int r = 0; r < L;) {
     int stop = 0;
-    if (!drive_rows(x, L, r, 0, stop, lane, ea, eb, load, row)) break;
+    if (!drive_rows(x, L, r, stop, lane, ea, eb, load, row)) break;
     // a value above RL (32766 without re-basing: an overflow)
     if (!reb || RL == 32766) {
       res.redo = true;
@@ -489,7 +485,7 @@ __device__ __forceinline__ int vit32_target(const int *emit, const int (&tr)[TR_
   };
   int ea[2 * Q], eb[2 * Q];
   int stop;
-  (void)drive_rows(x, L, 0, 0, stop, lane, ea, eb, load, row);
+  (void)drive_rows(x, L, 0, stop, lane, ea, eb, load, row);
   const int m = wave_max_i32(accM);
   return fl32(fl32(m + ej) + mv);
 }
@@ -645,7 +641,7 @@ __device__ __forceinline__ float fwd_target(const float *emit, const FwdRegs<Q> 
   };
   float ea[2 * Q], eb[2 * Q];
   int stop;
-  (void)drive_rows(x, L, 0, 0, stop, lane, ea, eb, load, row);
+  (void)drive_rows(x, L, 0, stop, lane, ea, eb, load, row);
   return (float)(log((double)C * (double)move) + (double)shift * M_LN2);
 }
 
@@ -1090,8 +1086,9 @@ hipError_t launch_search_group(const DevProfile *P, const DevDb *db, const DevOu
   }
   // The tails start after every MSV launch.  Started right after their own
   // group's launch, they share the CUs with the later MSV launches, which
-  // absorb that (their waves take targets from a work counter), but the
-  // group still took longer (C4: 350.7 against 345.0 ms).
+  // absorb that (their waves take targets from work counters), but the
+  // group still took longer (64 profiles of 50 to 400 nodes, with an MSV kernel
+  // of three instructions per pair of cells: 350.7 against 345.0 ms).
   for (int i = 0; i < n && e == hipSuccess; i++) tail(i);
   // every search's tail joins the caller's stream
   for (int i = 0; i < n && e == hipSuccess; i++) ok(hipStreamWaitEvent(s, y[i]->tail_done, 0));
