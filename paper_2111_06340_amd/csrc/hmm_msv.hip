@@ -168,18 +168,14 @@ struct MsvTab {
     }
   }
 
-  // Profile g's vectors alone, at any diagonal offset r in [0, P/2].
+  // Diagonal: profile g's vectors alone, at any offset r in [0, P/2].
   __device__ __forceinline__ void load_one(uint32_t (&c)[Q], int a, int r, int g) const {
     const uint32_t *row = (const uint32_t *)lds + a * kRow;
 #pragma unroll
     for (int q = 0; q < Q; q++) {
-      if constexpr (DIAG) {
-        const bool pair = kWide && (q < Q / 2 * 2);
-        const int k = pair ? (q / 2) * 2 * kWave + 2 * lane + (q & 1) : q * kWave + lane;
-        c[q] = row[(k + r) * G + g];
-      } else {
-        c[q] = row[msv_stripe_dword(Q, q, lane)];
-      }
+      const bool pair = kWide && (q < Q / 2 * 2);
+      const int k = pair ? (q / 2) * 2 * kWave + 2 * lane + (q & 1) : q * kWave + lane;
+      c[q] = row[(k + r) * G + g];
     }
   }
 };
@@ -381,16 +377,20 @@ struct MsvResult {
   bool ovf;
 };
 
-// One target against profile g of the tables, on w.  Rows run in batches of
-// B; after each, one test finds out whether some cell has reached the trigger
-// value T (the smallest that changes xB or overflows).  If so the batch is run
-// again from its first row with a test after every row: the row that fired
-// updates xJ and xB and re-bases w to the new Bx.
+// One target against profile g of the tables, on w.  The rows test whether some
+// cell has reached the trigger value T (the smallest that changes xB or
+// overflows); the row that fired updates xJ and xB and re-bases w to the new Bx.
+//  diagonal: rows run in batches of B, with one test after each; if it finds such
+//    a cell the batch is run again from its first row, with a test after every
+//    row.
+//  striped: a test after every row; no state is kept to run one again, and the
+//    entries are read four vectors at a time.  A long profile's hits stay in this
+//    pass while the other targets' waves are done: M = 1,900 x 50,000 targets,
+//    0.4 % of them homologs, 1.61 ms (batches and dword reads 1.94; without
+//    homologs 1.04), M = 3,072 2.76 (3.25).
 template <int Q, bool DIAG, int G>
 __device__ __forceinline__ MsvResult msv_exact(const MsvTab<Q, DIAG, G> &tab, int g, const DevProfile &P,
                                                const uint8_t *x, int L, int mv, int lane) {
-  constexpr int kHalf = Q * kWave;
-  constexpr int B = Q <= 6 ? 4 : Q <= 12 ? 2 : 1;
   auto splat = [](int v) -> uint32_t { return (uint32_t)uni((int)as_u(h2_splat(v))); };
   const int entry8 = P.entry8, exit8 = P.exit8;
   const int ovf_line = 255 - P.bias8;
@@ -418,60 +418,74 @@ __device__ __forceinline__ MsvResult msv_exact(const MsvTab<Q, DIAG, G> &tab, in
     m[Q] = acc;
     acc = h2_max_tree(m);
   };
+  // after a row that fired: false if it overflowed
+  auto settle = [&]() -> bool {
+    const int m = wave_max_i32(h2_hmax(acc)) + Bx;   // largest cell so far
+    if (m >= ovf_line) return false;
+    xJt = max(xJt, max(m - exit8, 0));
+    const int nBx = min(max(max(base, max(xJt - mv, 0)) - entry8, 0), ovf_line);
+    if (nBx != Bx) {   // re-base w and the running maximum to the new Bx
+      const h16x2 d = as_h2(splat(Bx - nBx));
+#pragma unroll
+      for (int q = 0; q < Q; q++) w[q] += d;
+      acc += d;
+      Bx = nBx;
+      nbx = splat(-Bx);
+    }
+    thr = trigger_thr();
+    return true;
+  };
   const uint32_t *p = (const uint32_t *)x;
   uint32_t cur = 0, wd = 0;
-  int dr = 0;   // row modulo P/2 (diagonal)
-  for (int r = 0; r < L; r += B) {
+  // residue r, asked for in order (those past the target's end, up to three, are
+  // in its last dword and select a table row that no row uses)
+  auto code = [&](int r) -> int {
     if ((r & 255) == 0) cur = p[(r >> 2) + lane];
-    if ((r & 3) == 0) wd = (uint32_t)__builtin_amdgcn_readlane((int)cur, (r >> 2) & 63);
-    uint32_t c[B][Q];
+    wd = (r & 3) == 0 ? (uint32_t)__builtin_amdgcn_readlane((int)cur, (r >> 2) & 63) : wd >> 8;
+    return (int)(wd & 0xffu);
+  };
+  if constexpr (DIAG) {
+    constexpr int kHalf = Q * kWave;
+    constexpr int B = Q <= 6 ? 4 : 2;
+    int dr = 0;   // row modulo P/2
+    for (int r = 0; r < L; r += B) {
+      uint32_t c[B][Q];
 #pragma unroll
-    for (int k = 0; k < B; k++) {
-      tab.load_one(c[k], (int)(wd & 0xffu), dr + (DIAG ? k : 0), g);
-      wd >>= 8;
-    }
-    const h16x2 acc0 = acc;
-    h16x2 w0[Q];
+      for (int k = 0; k < B; k++) tab.load_one(c[k], code(r + k), dr + k, g);
+      const h16x2 acc0 = acc;
+      h16x2 w0[Q];
 #pragma unroll
-    for (int q = 0; q < Q; q++) w0[q] = w[q];
-    const int rows = min(B, L - r);
-    if (rows == B) {
+      for (int q = 0; q < Q; q++) w0[q] = w[q];
+      const int rows = min(B, L - r);
+      if (rows == B) {
 #pragma unroll
-      for (int k = 0; k < B; k++) row(c[k]);
-    }
-    if (rows < B || __builtin_expect(fired(), 0)) {
+        for (int k = 0; k < B; k++) row(c[k]);
+      }
+      if (rows < B || __builtin_expect(fired(), 0)) {
 #pragma unroll
-      for (int q = 0; q < Q; q++) w[q] = w0[q];
-      acc = acc0;
+        for (int q = 0; q < Q; q++) w[q] = w0[q];
+        acc = acc0;
 #pragma unroll
-      for (int k = 0; k < B; k++) {
-        if (k < rows) {
-          row(c[k]);
-          if (fired()) {
-            const int m = wave_max_i32(h2_hmax(acc)) + Bx;   // largest cell so far
-            if (m >= ovf_line) return MsvResult{255, true};
-            xJt = max(xJt, max(m - exit8, 0));
-            const int nBx = min(max(max(base, max(xJt - mv, 0)) - entry8, 0), ovf_line);
-            if (nBx != Bx) {   // re-base w and the running maximum to the new Bx
-              const h16x2 d = as_h2(splat(Bx - nBx));
-#pragma unroll
-              for (int q = 0; q < Q; q++) w[q] += d;
-              acc += d;
-              Bx = nBx;
-              nbx = splat(-Bx);
-            }
-            thr = trigger_thr();
+        for (int k = 0; k < B; k++) {
+          if (k < rows) {
+            row(c[k]);
+            if (fired() && !settle()) return MsvResult{255, true};
           }
         }
       }
-    }
-    if constexpr (DIAG) {
       dr += B;
       if (dr == kHalf) {   // the halves of each state dword swap diagonals
         dr = 0;
 #pragma unroll
         for (int q = 0; q < Q; q++) w[q] = as_h2(__builtin_amdgcn_alignbit(as_u(w[q]), as_u(w[q]), 16));
       }
+    }
+  } else {
+    for (int r = 0; r < L; r++) {
+      uint32_t c[Q];
+      tab.template load<0>(c, code(r), 0);
+      row(c);
+      if (__builtin_expect(fired(), 0) && !settle()) return MsvResult{255, true};
     }
   }
   const int m = wave_max_i32(h2_hmax(acc)) + Bx;
