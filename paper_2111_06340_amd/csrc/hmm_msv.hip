@@ -380,14 +380,15 @@ struct MsvResult {
 // One target against profile g of the tables, on w.  The rows test whether some
 // cell has reached the trigger value T (the smallest that changes xB or
 // overflows); the row that fired updates xJ and xB and re-bases w to the new Bx.
-//  diagonal: rows run in batches of B, with one test after each; if it finds such
-//    a cell the batch is run again from its first row, with a test after every
-//    row.
-//  striped: a test after every row; no state is kept to run one again, and the
-//    entries are read four vectors at a time.  A long profile's hits stay in this
-//    pass while the other targets' waves are done: M = 1,900 x 50,000 targets,
-//    0.4 % of them homologs, 1.61 ms (batches and dword reads 1.94; without
-//    homologs 1.04), M = 3,072 2.76 (3.25).
+//  up to 12 vectors: rows run in batches of B, with one test after each; if it
+//    finds such a cell the batch is run again from its first row, with a test
+//    after every row.
+//  above: a test after every row; no state is kept to run one again.  A long
+//    profile's hits stay in this pass while the other targets' waves are done:
+//    M = 1,900 x 50,000 targets, 0.4 % of them homologs, 1.61 ms (with a copy of
+//    the state and dword reads 1.94; without homologs 1.04), M = 3,072 2.76 (3.25).
+//    (At 9 vectors batches are faster: 30,000 targets of up to 5,000 residues by
+//    1,025 nodes, a search 6.42 with them before, 6.37 now, row by row 6.5 ms.)
 template <int Q, bool DIAG, int G>
 __device__ __forceinline__ MsvResult msv_exact(const MsvTab<Q, DIAG, G> &tab, int g, const DevProfile &P,
                                                const uint8_t *x, int L, int mv, int lane) {
@@ -444,14 +445,19 @@ __device__ __forceinline__ MsvResult msv_exact(const MsvTab<Q, DIAG, G> &tab, in
     wd = (r & 3) == 0 ? (uint32_t)__builtin_amdgcn_readlane((int)cur, (r >> 2) & 63) : wd >> 8;
     return (int)(wd & 0xffu);
   };
-  if constexpr (DIAG) {
+  constexpr int B = Q <= 6 ? 4 : Q <= 12 ? 2 : 1;
+  if constexpr (B > 1) {
     constexpr int kHalf = Q * kWave;
-    constexpr int B = Q <= 6 ? 4 : 2;
-    int dr = 0;   // row modulo P/2
+    int dr = 0;   // diagonal: row modulo P/2
     for (int r = 0; r < L; r += B) {
       uint32_t c[B][Q];
 #pragma unroll
-      for (int k = 0; k < B; k++) tab.load_one(c[k], code(r + k), dr + k, g);
+      for (int k = 0; k < B; k++) {
+        if constexpr (DIAG)
+          tab.load_one(c[k], code(r + k), dr + k, g);
+        else
+          tab.template load<0>(c[k], code(r + k), 0);
+      }
       const h16x2 acc0 = acc;
       h16x2 w0[Q];
 #pragma unroll
@@ -474,7 +480,7 @@ __device__ __forceinline__ MsvResult msv_exact(const MsvTab<Q, DIAG, G> &tab, in
         }
       }
       dr += B;
-      if (dr == kHalf) {   // the halves of each state dword swap diagonals
+      if (DIAG && dr == kHalf) {   // the halves of each state dword swap diagonals
         dr = 0;
 #pragma unroll
         for (int q = 0; q < Q; q++) w[q] = as_h2(__builtin_amdgcn_alignbit(as_u(w[q]), as_u(w[q]), 16));
