@@ -173,7 +173,8 @@ int hmm_db_share(const hmm_db *db, hmm_db **out);
  * (hmm_db_pipeline) runs the MSV kernels there and Viterbi and Forward of
  * each chunk on a stream owned by the database handle.  That search, and one
  * by a profile whose int16 overflows the Viterbi kernel does not score exactly
- * by itself, runs the int32 rescore on another such stream, beside Forward.
+ * by itself, runs the int32 rescore and Forward beside each other, one of
+ * them on another such stream.
  * These streams are forked from `stream` and joined back before the search
  * ends, so all of the search's work is ordered on `stream`.
  * Searches on one database are serialised by the library (a search on a
@@ -341,7 +342,7 @@ int hmm_db_stage_timing(hmm_db *db, int32_t capacity);
 /* Stage durations (ms) of the recorded searches, oldest first:
  * out_ms[4*i + s] for search i and stage s = MSV, Viterbi int16, int32
  * rescore, Forward (each including its small list/counter kernels).  The
- * rescore and Forward may run concurrently (the rescore on a stream internal
+ * rescore and Forward may run concurrently (one of them on a stream internal
  * to the database, forked from and joined back into the search stream): both
  * are timed from the end of the int16 Viterbi stage, the rescore to its own
  * end and Forward to the end of both, so Forward's figure is the time the

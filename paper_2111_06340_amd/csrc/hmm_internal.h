@@ -168,7 +168,7 @@ struct DevOut {
   float *bias;                  // optional bias scores
   int32_t bias_filter;          // 1: composition-bias filter between MSV and Viterbi
   int32_t fused_tail;           // 1: the stages after MSV as one kernel where an instance exists
-  int32_t rescore_apart;        // 1: the int32 rescore on its own stream, beside Forward
+  int32_t rescore_apart;        // 1: the int32 rescore and Forward beside each other
 };
 
 // Posterior decoding (hmm_decode): outputs and per-wave scratch.
@@ -230,7 +230,8 @@ constexpr int kMaxChunks = 8;
 // Streams and events that order one database handle's searches.
 struct SearchSync {
   hipStream_t tail = nullptr;           // Viterbi and Forward of the chunks
-  hipStream_t aux = nullptr;            // int32 rescore beside Forward (DevOut::rescore_apart)
+  hipStream_t aux = nullptr;            // their int32 rescore; or Forward beside the rescore of a
+                                        // search that keeps to its own stream (rescore_apart)
   hipEvent_t msv_done[kMaxChunks] = {}; // recorded on the search stream
   hipEvent_t vit_done[kMaxChunks] = {}; // recorded on tail
   hipEvent_t aux_done = nullptr, tail_done = nullptr;

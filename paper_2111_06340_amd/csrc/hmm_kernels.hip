@@ -979,14 +979,19 @@ hipError_t launch_search(const DevProfile &P, const DevDb *chunk, int K, const D
 // stream waits for y.tail_done when `join` is set; a group joins all of its
 // searches at its end).  With `o.fused_tail` and a profile that has a fused
 // instance, one kernel takes all three stages.  Otherwise the rescore runs
-// beside Forward on a stream of its own (an overflow passes the Viterbi filter
-// whatever its exact score, so Forward needs nothing from it).  Only a search
-// that keeps to the search stream and whose overflows are re-based (not
-// o.rescore_apart) runs it before Forward: there it has nothing to do in
+// beside Forward (an overflow passes the Viterbi filter whatever its exact score,
+// so Forward needs nothing from it), one of them on the handle's other stream.
+// Only a search that keeps to the search stream and whose overflows are re-based
+// (not o.rescore_apart) runs it before Forward: there it has nothing to do in
 // ordinary searches, and an empty launch takes 4 us, a fork and join of streams
 // 10 to 20.  (In a group of 12 the searches' streams overlap each other: 10.04 ms
-// with the empty launches in line, 9.94 beside Forward.)  `swap` exchanges the
-// two streams.
+// with the empty launches in line, 9.94 beside Forward.)  A search that keeps to
+// the search stream has its rescore there and Forward on the other one, which
+// starts later: the blocks of whichever starts first hold the CUs until it ends,
+// and with many overflows that should be the rescore, which ends sooner (10,000
+// homologs, M = 1,500: rescore first 26.4, Forward first 28.0 ms; 5,000 at M =
+// 2,500 39.0 and 40.0; 100,000 targets with 0.2 % homologs 7.3 and 7.35).  `swap`
+// exchanges the two streams.
 hipError_t launch_tail(const DevProfile &P, const DevDb *chunk, int K, const DevOut &o, hipStream_t s,
                        const SearchSync &y, hipEvent_t *ev, bool join, bool swap) {
   hipError_t e = hipSuccess;
@@ -1001,22 +1006,18 @@ hipError_t launch_tail(const DevProfile &P, const DevDb *chunk, int K, const Dev
   const bool own = K > 1 || !join;
   const bool apart = (o.rescore_apart || own) && !fused;
   const hipStream_t ts = !own ? s : swap ? y.aux : y.tail, as = swap ? y.tail : y.aux;
+  const hipStream_t rs = own ? as : ts, fs = apart && !own ? as : ts;   // the rescore's and Forward's
   for (int k = 0; k < K && e == hipSuccess; k++) {
     const bool any = chunk[k].n > 0;
     const DevDb &ck = chunk[k];
     if (own && !ok(hipStreamWaitEvent(ts, y.msv_done[k], 0))) break;
     if (any && !ok(fused ? dispatch_tail_fused(P, ck, o, ts) : dispatch_vit16(P, ck, o, ts))) break;
     if (k == K - 1) mark(2, ts);
-    if (apart) {
-      if (!ok(hipEventRecord(y.vit_done[k], ts)) || !ok(hipStreamWaitEvent(as, y.vit_done[k], 0))) break;
-      if (any && !ok(dispatch_vit32(P, ck, o, as))) break;
-    }
-    if (fused) continue;
-    if (any && !apart && !ok(dispatch_vit32(P, ck, o, ts))) break;
-    if (k == K - 1 && !apart) mark(3, ts);
-    if (any && !ok(dispatch_fwd(P, ck, o, ts))) break;
+    if (apart && (!ok(hipEventRecord(y.vit_done[k], ts)) || !ok(hipStreamWaitEvent(as, y.vit_done[k], 0)))) break;
+    if (any && !fused && !ok(dispatch_vit32(P, ck, o, rs))) break;
+    if (k == K - 1) mark(3, fused ? ts : rs);
+    if (any && !fused && !ok(dispatch_fwd(P, ck, o, fs))) break;
   }
-  if (apart || fused) mark(3, apart ? as : ts);
   if (apart && ok(hipEventRecord(y.aux_done, as))) ok(hipStreamWaitEvent(ts, y.aux_done, 0));
   // chunk 0 starts at sorted index 0: its sorted arrays are the whole
   // database's
