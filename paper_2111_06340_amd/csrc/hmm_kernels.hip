@@ -220,6 +220,7 @@ __device__ __forceinline__ VitResult vit16_target(const uint32_t *__restrict__ e
   uint32_t tau2 = floor_of(sat16(mv + entry));
   const bool reb = kRebase16<Q> && mv + entry >= kNeg16 + P.rebase_w;
   int RL = reb ? 32766 - P.s_max : 32766;
+  uint32_t rl2 = splat16(RL);
   int off = 0, top = 0;   // top: the largest true value at a re-basing
   // trigger: some accM > tm1, or some accI > RL, i.e. accI + iadj > tm1
   uint32_t tm1 = splat16(min(-ej, 32766));
@@ -297,7 +298,7 @@ __device__ __forceinline__ VitResult vit16_target(const uint32_t *__restrict__ e
     const uint32_t acc = kRebase16<Q> ? i16_max(accM, i16_adds(accI, iadj)) : accM;
     if (__builtin_expect(any_lane(i16_max(acc, tm1) != tm1), 0)) {
       const int m = wave_max_i32(hmax16(accM));
-      if (m > RL || (kRebase16<Q> && any_lane(i16_max(accI, splat16(RL)) != splat16(RL)))) return true;
+      if (m > RL || (kRebase16<Q> && any_lane(i16_max(accI, rl2) != rl2))) return true;
       settle(m);
     }
     return false;
@@ -321,7 +322,8 @@ __device__ __forceinline__ VitResult vit16_target(const uint32_t *__restrict__ e
         res.redo = true;
         break;
       }
-      RL = 32766;   // no value has reached 32767: on without re-basing
+      RL = 32766;
+      rl2 = splat16(RL);   // no value has reached 32767: on without re-basing
       sh = 0;
     }
     top = max(top, hi + off);
