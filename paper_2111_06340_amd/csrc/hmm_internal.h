@@ -230,8 +230,8 @@ constexpr int kMaxChunks = 8;
 // Streams and events that order one database handle's searches.
 struct SearchSync {
   hipStream_t tail = nullptr;           // Viterbi and Forward of the chunks
-  hipStream_t aux = nullptr;            // their int32 rescore; or Forward beside the rescore of a
-                                        // search that keeps to its own stream (rescore_apart)
+  hipStream_t aux = nullptr;            // the int32 rescore beside Forward (rescore_apart), or
+                                        // Forward beside the rescore (see launch_tail)
   hipEvent_t msv_done[kMaxChunks] = {}; // recorded on the search stream
   hipEvent_t vit_done[kMaxChunks] = {}; // recorded on tail
   hipEvent_t aux_done = nullptr, tail_done = nullptr;

@@ -987,13 +987,15 @@ hipError_t launch_search(const DevProfile &P, const DevDb *chunk, int K, const D
 // (not o.rescore_apart) runs it before Forward: there it has nothing to do in
 // ordinary searches, and an empty launch takes 4 us, a fork and join of streams
 // 10 to 20.  (In a group of 12 the searches' streams overlap each other: 10.04 ms
-// with the empty launches in line, 9.94 beside Forward.)  A search that keeps to
-// the search stream has its rescore there and Forward on the other one, which
-// starts later: the blocks of whichever starts first hold the CUs until it ends,
-// and with many overflows that should be the rescore, which ends sooner (10,000
-// homologs, M = 1,500: rescore first 26.4, Forward first 28.0 ms; 5,000 at M =
-// 2,500 39.0 and 40.0; 100,000 targets with 0.2 % homologs 7.3 and 7.35).  `swap`
-// exchanges the two streams.
+// with the empty launches in line, 9.94 beside Forward.)  Which of the two keeps
+// to the search stream starts first and ends without waiting for a join, and its
+// blocks hold the CUs until it ends.  From 20 vectors per lane on that is the
+// rescore, the longer one per target: 10,000 homologs at M = 1,500 26.4 ms,
+// Forward first 28.0; 30,000 targets with 0.2 % homologs at M = 2,500 6.70 and
+// 6.90, at M = 1,300 2.50 and 2.53; 1,000 open at M = 2,500 2.88 and 3.02.  Below, it
+// is Forward: 30,000 with 1 % homologs at M = 800 1.42, rescore first 1.50, at M =
+// 1,000 1.69 and 1.72; 300 open at M = 800 1.09 and 1.12.  `swap` exchanges the two
+// streams.
 hipError_t launch_tail(const DevProfile &P, const DevDb *chunk, int K, const DevOut &o, hipStream_t s,
                        const SearchSync &y, hipEvent_t *ev, bool join, bool swap) {
   hipError_t e = hipSuccess;
@@ -1008,7 +1010,8 @@ hipError_t launch_tail(const DevProfile &P, const DevDb *chunk, int K, const Dev
   const bool own = K > 1 || !join;
   const bool apart = (o.rescore_apart || own) && !fused;
   const hipStream_t ts = !own ? s : swap ? y.aux : y.tail, as = swap ? y.tail : y.aux;
-  const hipStream_t rs = own ? as : ts, fs = apart && !own ? as : ts;   // the rescore's and Forward's
+  const bool rescore_first = apart && !own && P.Q32 >= 20;
+  const hipStream_t rs = apart && !rescore_first ? as : ts, fs = rescore_first ? as : ts;   // the rescore's and Forward's
   for (int k = 0; k < K && e == hipSuccess; k++) {
     const bool any = chunk[k].n > 0;
     const DevDb &ck = chunk[k];
