@@ -438,26 +438,25 @@ __device__ __forceinline__ MsvResult msv_exact(const MsvTab<Q, DIAG, G> &tab, in
   };
   const uint32_t *p = (const uint32_t *)x;
   uint32_t cur = 0, wd = 0;
-  // residue r, asked for in order (those past the target's end, up to three, are
-  // in its last dword and select a table row that no row uses)
-  auto code = [&](int r) -> int {
-    if ((r & 255) == 0) cur = p[(r >> 2) + lane];
-    wd = (r & 3) == 0 ? (uint32_t)__builtin_amdgcn_readlane((int)cur, (r >> 2) & 63) : wd >> 8;
-    return (int)(wd & 0xffu);
-  };
+  constexpr int kHalf = Q * kWave;
   constexpr int B = Q <= 6 ? 4 : Q <= 12 ? 2 : 1;
-  if constexpr (B > 1) {
-    constexpr int kHalf = Q * kWave;
-    int dr = 0;   // diagonal: row modulo P/2
-    for (int r = 0; r < L; r += B) {
-      uint32_t c[B][Q];
+  int dr = 0;   // row modulo P/2 (diagonal)
+  for (int r = 0; r < L; r += B) {
+    if ((r & 255) == 0) cur = p[(r >> 2) + lane];
+    if ((r & 3) == 0) wd = (uint32_t)__builtin_amdgcn_readlane((int)cur, (r >> 2) & 63);
+    uint32_t c[B][Q];
 #pragma unroll
-      for (int k = 0; k < B; k++) {
-        if constexpr (DIAG)
-          tab.load_one(c[k], code(r + k), dr + k, g);
-        else
-          tab.template load<0>(c[k], code(r + k), 0);
-      }
+    for (int k = 0; k < B; k++) {
+      if constexpr (DIAG)
+        tab.load_one(c[k], (int)(wd & 0xffu), dr + k, g);
+      else
+        tab.template load<0>(c[k], (int)(wd & 0xffu), 0);
+      wd >>= 8;
+    }
+    if constexpr (B == 1) {
+      row(c[0]);
+      if (__builtin_expect(fired(), 0) && !settle()) return MsvResult{255, true};
+    } else {
       const h16x2 acc0 = acc;
       h16x2 w0[Q];
 #pragma unroll
@@ -479,19 +478,14 @@ __device__ __forceinline__ MsvResult msv_exact(const MsvTab<Q, DIAG, G> &tab, in
           }
         }
       }
+    }
+    if constexpr (DIAG) {
       dr += B;
-      if (DIAG && dr == kHalf) {   // the halves of each state dword swap diagonals
+      if (dr == kHalf) {   // the halves of each state dword swap diagonals
         dr = 0;
 #pragma unroll
         for (int q = 0; q < Q; q++) w[q] = as_h2(__builtin_amdgcn_alignbit(as_u(w[q]), as_u(w[q]), 16));
       }
-    }
-  } else {
-    for (int r = 0; r < L; r++) {
-      uint32_t c[Q];
-      tab.template load<0>(c, code(r), 0);
-      row(c);
-      if (__builtin_expect(fired(), 0) && !settle()) return MsvResult{255, true};
     }
   }
   const int m = wave_max_i32(h2_hmax(acc)) + Bx;
