@@ -58,8 +58,9 @@ struct WorkQueue {
   int n, n0, lanes, c;
   __device__ __forceinline__ WorkQueue(const DevDb &db, int stage, int n_) : n(n_) {
     n0 = PER_BLOCK ? (int)gridDim.x : num_waves();
-    lanes = PER_BLOCK || (int)gridDim.x < 8 * kWorkLanes ? 1 : kWorkLanes;
-    c = (int)blockIdx.x % lanes;
+    const bool one = PER_BLOCK || (int)gridDim.x < 8 * kWorkLanes;
+    lanes = one ? 1 : kWorkLanes;
+    c = one ? 0 : (int)blockIdx.x % kWorkLanes;
     work = db.counters + CNT_WORK + (stage * kWorkLanes + c) * kWorkStride;
   }
   __device__ __forceinline__ int first() const {
