@@ -846,11 +846,11 @@ int hmm_db_upload(const uint8_t *residues, const int64_t *offsets, int64_t n, hm
   memcpy(db->chunk_at, chunk_at, sizeof chunk_at);
   // One chunk: each MSV kernel fills every CU's LDS, so a chunk's Viterbi
   // runs mostly after the next MSV anyway, and every chunk adds an MSV
-  // launch and its drain.  Since the MSV waves take their targets from a
-  // work counter (no wave is left with a slow share), the sequential search
-  // is the fastest measured: 348M residues, M = 734: 14.34 ms against 14.64
-  // for two chunks and 15.17 for three; 707M residues, M = 2500: 111.0 ms
-  // against 111.8 for two, 112.9 for three and 113.3 for four.
+  // launch and its drain.  Since the MSV waves take their targets from
+  // work counters (no wave is left with a slow share), the sequential search
+  // is the fastest measured: 348M residues, M = 734: 10.65 ms against 11.41
+  // for two chunks and 11.69 for three; 707M residues, M = 2500: 88.3 ms
+  // against 88.4 for two, 89.1 for three and 89.3 for four.
   db->chunks = 1;
   db->data = new (std::nothrow) hmm_db_data();
   if (!db->data) {
